@@ -62,12 +62,32 @@ size_t prep_ws(const vc_shape* s) {
   return 2 * align256(BH * T * kD * 4) + align256(BH * kD * 4);
 }
 
+// At least what vc_attn_group carves up below (callers hold buffers of this size).
 size_t group_ws(const vc_shape* s, const vc_group_opts* g) {
   if (g->mode != VC_GROUP_KMEANS) return 0;
   const size_t BH = (size_t)s->B * s->H, N = s->N, K = g->k, nblk = blocks_of(s->N, 256);
   return align256(BH * N * kD) + align256(BH * 4) + align256(BH * K * kD * 4) + align256(BH * nblk * K * kD * 4) +
          2 * align256(BH * nblk * K * 4) + align256(BH * 64 * kD) +
          align256(BH * 64 * 4);
+}
+
+// Tokens per k-means assignment workgroup (a multiple of 256, at most 65536: the member sums, times
+// 128, stay in int32). A workgroup of a round costs about 8 steps of 256 tokens (0.56 us each) for its
+// centroids, its sums and the launch, and each of the 256 CUs holds one, so the choice is the step
+// count s with the smallest ceil(workgroups / 256) (8 + s). Measured (us, cold grouping, 8 rounds):
+// 12 heads of 32760 tokens 256-token workgroups 264, 1024 159, 1792 and 2048 130, 4096 163; 24 heads
+// of 5850: 512 115, 1024 83, 2048 106; one head of 12150: 256 58, 1024 74.
+int assign_tokens(int BH, int N) {
+  int best = 1;
+  long long cost = 1LL << 62;
+  for (int s = 1; s <= 256 && 256 * (s - 1) < N; ++s) {
+    const long long wgs = (long long)BH * blocks_of(N, 256 * s), c = (wgs + 255) / 256 * (8 + s);
+    if (c <= cost) {
+      cost = c;
+      best = s;
+    }
+  }
+  return 256 * best;
 }
 
 vc_status hip_status(hipError_t e) {
@@ -201,9 +221,11 @@ vc_status vc_attn_group(const vc_shape* shape, const vc_group_opts* gopts, const
   a.cube_t = gopts->cube[0];
   a.cube_h = gopts->cube[1];
   a.cube_w = gopts->cube[2];
+  a.BH = (int)BH;
   a.nblk = blocks_of(shape->N, 256);
-  a.npart = blocks_of(shape->N, 1024);
-  a.nlab = a.k;
+  a.sums_head = (a.k * (kD + 1) + 3) & ~3;
+  a.nsort = blocks_of(shape->N, 1024);
+  a.atok = assign_tokens((int)BH, shape->N);
   if (km) {
     char* p = static_cast<char*>(ws);
     const size_t N = shape->N, K = a.k, nblk = a.nblk;
@@ -211,17 +233,13 @@ vc_status vc_attn_group(const vc_shape* shape, const vc_group_opts* gopts, const
     p += align256(BH * N * kD);
     a.scale = reinterpret_cast<float*>(p);
     p += align256(BH * 4);
-    a.cent = reinterpret_cast<int32_t*>(p);
+    a.cent8 = reinterpret_cast<int8_t*>(p);
     p += align256(BH * K * kD * 4);
     a.sums = reinterpret_cast<int32_t*>(p);
     p += align256(BH * nblk * K * kD * 4);
-    a.counts = reinterpret_cast<int32_t*>(p);
+    a.amax_part = reinterpret_cast<float*>(p);
     p += align256(BH * nblk * K * 4);
-    a.blockhist = reinterpret_cast<int32_t*>(p);
-    p += align256(BH * nblk * K * 4);
-    a.cent8 = reinterpret_cast<int8_t*>(p);
-    p += align256(BH * 64 * kD);
-    a.cnorm = reinterpret_cast<int32_t*>(p);
+    a.hist = reinterpret_cast<int32_t*>(p);
   }
   return hip_status(vc::launch_group(a, (int)BH, static_cast<hipStream_t>(stream)));
 }

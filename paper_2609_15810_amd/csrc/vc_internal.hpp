@@ -52,16 +52,18 @@ struct GroupArgs {
   const uint16_t* V;
   float* centroids;
   int32_t *labels, *perm, *inv_perm;
-  int8_t* codes;     // workspace: per-head INT8 codes of V [B*H][N][128]
-  float* scale;      // workspace: [B*H] amax (then scale)
-  int32_t* cent;     // workspace: [B*H][k][128] integer centroids
-  int8_t* cent8;     // workspace: [B*H][64][128] the same as int8, rows k.. zero
-  int32_t* cnorm;    // workspace: [B*H][64] their squared norms, rows k.. a padding value
-  int32_t* sums;     // workspace: [B*H][npart][k][128] member sums per assignment workgroup
-  int32_t* counts;   // workspace: [B*H][npart][k] member counts, later [B*H][nblk][k] label histograms
-  int32_t* blockhist;// workspace: [B*H][nblk][nlab] per-block label counts, then offsets
-  int N, F, Ht, Wd, k, iters, warm_start, mode, cube_t, cube_h, cube_w, nlab, nblk;
-  int npart;         // assignment workgroups per head (1024 tokens each)
+  // workspace (k-means)
+  int8_t* codes;      // [B*H][N][128] INT8 codes of V
+  float* scale;       // [B*H] max |V|
+  float* amax_part;   // [B*H][nblk] its partial maxima
+  int8_t* cent8;      // [2][B*H][k][128] the centroids of a round and the one before
+  int32_t* sums;      // [3][B*H][sums_head] member sums [k][128] and counts [k] of three rounds in turn
+  int32_t* hist;      // [B*H][nsort][k] final label counts per 1024 tokens
+  int BH, N, F, Ht, Wd, k, iters, warm_start, mode, cube_t, cube_h, cube_w;
+  int nblk;           // 256-token blocks per head
+  int sums_head;      // k * 129 rounded up to 16 bytes
+  int nsort;          // 1024-token blocks per head
+  int atok;           // tokens per assignment workgroup (a multiple of 256)
 };
 
 hipError_t launch_prep(const PrepArgs& a, int BH, hipStream_t s);
