@@ -57,27 +57,31 @@
 
 namespace vc {
 
-constexpr int NW = 8;             // waves per workgroup, 32 queries each (two per SIMD)
 constexpr int NXCD = 8;           // accelerator complex dies (each with its own L2)
-constexpr int NTH = 64 * NW;
-constexpr int NQ = 32 * NW;
 constexpr int TILE_BYTES = BLK * D;
 constexpr int VBUF_BYTES = TILE_BYTES + 2 * D;
-constexpr int KCOPIES = TILE_BYTES / 1024 / NW;  // 1 KB copies per wave per tile (V; INT8 K)
-constexpr int PAIR_COPIES = 2 * KCOPIES + 1;     // K and V pieces + the means
 constexpr int MX_CODE_BYTES = TILE_BYTES / 2;    // packed E2M1 codes of a 128-key tile
 constexpr int MX_SCALE_BYTES = BLK * D / 32;     // its E8M0 scale bytes, one per 32 channels
-static_assert(MX_CODE_BYTES / 1024 / NW == 1 && MX_SCALE_BYTES / NW <= 4 * 64,
-              "MXFP4 K tiles move as one 1 KB copy of codes and one 4-byte-per-lane copy of scales per wave");
 static_assert(MX_CODE_BYTES + MX_SCALE_BYTES <= TILE_BYTES, "an MXFP4 K tile fits a K buffer");
-constexpr int MEAN_LANES = 64 / NW;              // lanes copying 4 bytes of means each
+
+// Copies per wave of a workgroup of NW waves (32 queries each): 1 KB pieces of a tile of K (MXFP4:
+// of codes, and one piece of scales) and of V, and one of its means
+template <int NW, int QKF>
+struct Copies {
+  static constexpr int K = QKF == VC_QK_MXFP4 ? MX_CODE_BYTES / 1024 / NW + 1 : TILE_BYTES / 1024 / NW;
+  static constexpr int V = TILE_BYTES / 1024 / NW;
+  static constexpr int PAIR = K + V + 1;
+  static constexpr int MEAN_LANES = 64 / NW;   // lanes copying 4 bytes of means each
+  static_assert(MX_SCALE_BYTES / NW <= 4 * 64, "a wave's scales are at most 4 bytes per lane");
+};
 
 // s_waitcnt immediate for vmcnt(n) (bits 3:0 and 15:14), the other counters left at their maxima
 constexpr int vm_wait(int n) { return 0x3f70 | (n & 0xf) | ((n >> 4) << 14); }
 // wait until at most n pairs' copies of this wave are in flight
+template <int PAIR>
 __device__ __forceinline__ void wait_pairs(int n) {
-  if (n >= 2) __builtin_amdgcn_s_waitcnt(vm_wait(2 * PAIR_COPIES));
-  else if (n == 1) __builtin_amdgcn_s_waitcnt(vm_wait(PAIR_COPIES));
+  if (n >= 2) __builtin_amdgcn_s_waitcnt(vm_wait(2 * PAIR));
+  else if (n == 1) __builtin_amdgcn_s_waitcnt(vm_wait(PAIR));
   else __builtin_amdgcn_s_waitcnt(vm_wait(0));
 }
 
@@ -243,11 +247,117 @@ __device__ __forceinline__ int code4(const SV& s, int d4, float mul, float add) 
   }
 }
 
+// Position of workgroup id in the order in which the grid is worked through: the dispatcher deals
+// workgroups to the XCDs round-robin by linear id, and this bijection gives each XCD a contiguous
+// range, so that its L2 serves one or two heads' K/V tiles instead of every head's.
+__device__ __forceinline__ int xcd_order(int id, int total) {
+  const int x = id % NXCD, q = total / NXCD, r = total % NXCD;
+  return x * q + min(x, r) + id / NXCD;
+}
+
+// 32 bytes of a lane's E4M3 operand: two 16-byte halves 512 bytes apart
+__device__ __forceinline__ v8i load_f8op(const uint8_t* p) {
+  const u4 lo = *reinterpret_cast<const u4*>(p);
+  const u4 hi = *reinterpret_cast<const u4*>(p + 512);
+  return v8i{(int)lo[0], (int)lo[1], (int)lo[2], (int)lo[3], (int)hi[0], (int)hi[1], (int)hi[2], (int)hi[3]};
+}
+
+// Query operands of 32-row block rb of query block `block` (counted over all heads). INT8: four
+// 32-channel operands, scale sq per 128-row block; FP8: two 64-channel operands (a lane holds 32
+// channels of its query), scale sq; MXFP4: two 64-channel operands with the E8M0 bytes qsc[m] of the
+// lane's 32-channel blocks
+template <int QKF, typename QO, int NQO>
+__device__ __forceinline__ void load_queries(const FwdArgs& a, size_t block, int rb, int lane, QO (&qop)[NQO], float& sq,
+                                             int (&qsc)[2]) {
+  const int kh = lane >> 5, col = lane & 31;
+  if constexpr (QKF == VC_QK_FP8) {
+    const uint8_t* qblk = reinterpret_cast<const uint8_t*>(a.q) + block * TILE_BYTES;
+#pragma unroll
+    for (int m = 0; m < 2; ++m) qop[m] = load_f8op(qblk + ((((rb * 2 + m) * 2 + kh) * 2) * 32 + col) * 16);
+    sq = a.q_scale[block];
+  } else if constexpr (QKF == VC_QK_MXFP4) {
+    const uint8_t* qblk = reinterpret_cast<const uint8_t*>(a.q) + block * MX_CODE_BYTES;
+#pragma unroll
+    for (int m = 0; m < 2; ++m) qop[m] = *reinterpret_cast<const v4i*>(qblk + ((rb * 2 + m) * 2 + kh) * 512 + col * 16);
+    const uint2 w = *reinterpret_cast<const uint2*>(a.q_mxs + block * MX_SCALE_BYTES + lane * 8);
+    const uint32_t d = (rb & 2) ? w.y : w.x;
+#pragma unroll
+    for (int m = 0; m < 2; ++m) qsc[m] = (int)((d >> (8 * ((rb & 1) * 2 + m))) & 0xffu);
+  } else {
+    const int8_t* qblk = a.q + block * TILE_BYTES;
+#pragma unroll
+    for (int dc = 0; dc < 4; ++dc) qop[dc] = *reinterpret_cast<const v4i*>(qblk + ((rb * 4 + dc) * 2 + kh) * 512 + col * 16);
+    sq = a.q_scale[block];
+  }
+}
+
+// row-sum operand of the 16x16x128 FP8 product: A rows 0 and 8 are ones on k-groups 0 and 2
+// (B lanes 0..15 and 32..47: queries 0..15), rows 4 and 12 on k-groups 1 and 3 (queries
+// 16..31); C row 4(l/16), column l%16 then holds r of query l%32 in register 0 of lane l
+__device__ __forceinline__ v8i row_sum_ones(int lane) {
+  const int row = lane & 15, g = lane >> 4;
+  const bool on = ((row == 0 || row == 8) && !(g & 1)) || ((row == 4 || row == 12) && (g & 1));
+  const int w = on ? 0x38383838 : 0;
+  return v8i{w, w, w, w, w, w, w, w};
+}
+
+// O^T += M^T R for the tiles of slots 0 .. last_slot, R_t = r_t 2^(m_t - m_run), (r_t, m_t) at rm[32 t]
+// and mu_t / s_V as bf16 hi + lo in ub[0], ub[1].
+// k-slots 0..7 (lanes with kh = 0) carry R_hi = bf16(R), slots 8..15 (kh = 1) R_lo = bf16(R - R_hi)
+// (R - R_hi is exact in fp32, and fma(-kh, R_hi, R) is R itself for kh = 0), against mu_hi in the
+// first product and mu_lo in the second: the four cross terms of the two splits.
+__device__ __forceinline__ void add_means(v16f (&o)[4], const float2* rm, const uint16_t (*ub)[D][8], int last_slot,
+                                          float m_run, int kh, int col) {
+  const float khf = (float)kh;
+  float R[8];
+#pragma unroll
+  for (int t = 0; t < 8; ++t) {
+    const float2 e = rm[32 * t];
+    R[t] = t <= last_slot ? e.x * __builtin_amdgcn_exp2f(e.y - m_run) : 0.f;
+  }
+  bf16x8 b;
+#pragma unroll
+  for (int t = 0; t < 8; t += 2) {
+    const v2f hi = __builtin_convertvector(__builtin_convertvector((v2f){R[t], R[t + 1]}, bf16x2), v2f);
+    const v2f part = {__builtin_fmaf(-khf, hi[0], R[t]), __builtin_fmaf(-khf, hi[1], R[t + 1])};
+    const bf16x2 v = __builtin_convertvector(part, bf16x2);
+    b[t] = v[0];
+    b[t + 1] = v[1];
+  }
+#pragma unroll
+  for (int db = 0; db < 4; ++db) {
+    const int c = 32 * db + col;
+    const bf16x8 a_hi = *reinterpret_cast<const bf16x8*>(&ub[0][c][0]);
+    const bf16x8 a_lo = *reinterpret_cast<const bf16x8*>(&ub[1][c][0]);
+    o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a_hi, b, o[db], 0, 0, 0);
+    o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a_lo, b, o[db], 0, 0, 0);
+  }
+}
+
+// codes of tile t of query q into a.p_codes, dword w of chunk kc = keys 32(2kc + w/4) + 8(w%4) + 4kh .. +3
+__device__ __forceinline__ void store_codes(const FwdArgs& a, int bh, int q, int t, int kh, const v8i (&pc)[2]) {
+  uint8_t* row = a.p_codes + ((size_t)bh * a.N + q) * ((size_t)a.T * BLK) + (size_t)t * BLK + 4 * kh;
+#pragma unroll
+  for (int kc = 0; kc < 2; ++kc)
+#pragma unroll
+    for (int w = 0; w < 8; ++w) *reinterpret_cast<int*>(row + 32 * (2 * kc + (w >> 2)) + 8 * (w & 3)) = pc[kc][w];
+}
+
+// The wave's own LDS stores are in place for its other lanes' loads, and its loads done before later stores.
+__device__ __forceinline__ void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // DUMP: also write the probability codes of every tile to a.p_codes (a debugging variant; the
 // stores wait for all copies in flight, so it runs unpipelined)
-template <int PMODE, int QKF, bool DUMP>
-__global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(NW / 4, NW / 4))) void attn_fwd(FwdArgs a) {
+template <int PMODE, int QKF, int NW, bool DUMP>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_fwd(FwdArgs a) {
   constexpr bool I8 = QKF == VC_QK_INT8, F8 = QKF == VC_QK_FP8, MX = QKF == VC_QK_MXFP4;
+  constexpr int NTH = 64 * NW, NQ = 32 * NW;
+  using CP = Copies<NW, QKF>;
+  constexpr int KCOPIES = CP::K, VCOPIES = CP::V, PAIR_COPIES = CP::PAIR, MEAN_LANES = CP::MEAN_LANES;
   using SV = std::conditional_t<I8, v16i, v16f>;  // a lane's 16 scores of one 32-key block
   using QO = std::conditional_t<F8, v8i, v4i>;    // one Q or K operand of the score product
   // K_t in kb[t % 4] (MXFP4: codes, then scale bytes at MX_CODE_BYTES); V_t with its 128 bf16 block means in vb[t % 4]; mu_t / s_V as bf16 hi + lo
@@ -266,19 +376,9 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(NW / 4, NW 
   __shared__ float svs[D], inv_svs[D];
   __shared__ float m_first[NW][32];  // each query's running maximum after tile 0
 
-  // The dispatcher deals workgroups to the XCDs round-robin by linear id; the remap (a bijection
-  // when the count divides evenly) gives each XCD a contiguous range of (head, query tile) pairs,
-  // so its L2 serves one or two heads' K/V tiles instead of every head's (half the HBM fetches;
-  // the time is unchanged, the kernel is not memory-bound)
-  int qt = blockIdx.x, bh = blockIdx.y;
-  {
-    const int total = gridDim.x * gridDim.y, id = blockIdx.x + gridDim.x * blockIdx.y;
-    if (total % NXCD == 0) {
-      const int l = (id % NXCD) * (total / NXCD) + id / NXCD;
-      qt = l % gridDim.x;
-      bh = l / gridDim.x;
-    }
-  }
+  // half the HBM fetches of the plain order; the time is unchanged, the kernel is not memory-bound
+  const int wg = a.first + xcd_order(blockIdx.x, gridDim.x);
+  const int per_head = (a.N + NQ - 1) / NQ, bh = wg / per_head, qt = wg - bh * per_head;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int kh = lane >> 5, col = lane & 31;
@@ -288,38 +388,10 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(NW / 4, NW 
   const int gq = NW * qt + wave;  // global 32-query group
   const int qblock = min(gq >> 2, T - 1);
   const int qrb = gq & 3;         // the group's 32-row block within its 128-row block
-  // INT8: four 32-channel operands, scale sq per 128-row block; FP8: two 64-channel operands (a
-  // lane holds 32 channels of its query), scale sq; MXFP4: two 64-channel operands with the E8M0
-  // bytes qsc[m] of the lane's 32-channel blocks
   QO qop[I8 ? 4 : 2];
   float sq = 1.f;
   int qsc[2] = {0, 0};
-  if constexpr (F8) {
-    const uint8_t* qblk = reinterpret_cast<const uint8_t*>(a.q) + (tile0 + qblock) * TILE_BYTES;
-#pragma unroll
-    for (int m = 0; m < 2; ++m) {
-      const uint8_t* p = qblk + ((((qrb * 2 + m) * 2 + kh) * 2) * 32 + col) * 16;
-      const u4 lo = *reinterpret_cast<const u4*>(p);
-      const u4 hi = *reinterpret_cast<const u4*>(p + 512);
-      qop[m] = v8i{(int)lo[0], (int)lo[1], (int)lo[2], (int)lo[3], (int)hi[0], (int)hi[1], (int)hi[2], (int)hi[3]};
-    }
-    sq = a.q_scale[tile0 + qblock];
-  } else if constexpr (MX) {
-    const uint8_t* qblk = reinterpret_cast<const uint8_t*>(a.q) + (tile0 + qblock) * MX_CODE_BYTES;
-#pragma unroll
-    for (int m = 0; m < 2; ++m)
-      qop[m] = *reinterpret_cast<const v4i*>(qblk + ((qrb * 2 + m) * 2 + kh) * 512 + col * 16);
-    const uint2 w = *reinterpret_cast<const uint2*>(a.q_mxs + (tile0 + qblock) * MX_SCALE_BYTES + lane * 8);
-    const uint32_t d = (qrb & 2) ? w.y : w.x;
-#pragma unroll
-    for (int m = 0; m < 2; ++m) qsc[m] = (int)((d >> (8 * ((qrb & 1) * 2 + m))) & 0xffu);
-  } else {
-    const int8_t* qblk = a.q + (tile0 + qblock) * TILE_BYTES;
-#pragma unroll
-    for (int dc = 0; dc < 4; ++dc)
-      qop[dc] = *reinterpret_cast<const v4i*>(qblk + ((qrb * 4 + dc) * 2 + kh) * 512 + col * 16);
-    sq = a.q_scale[tile0 + qblock];
-  }
+  load_queries<QKF>(a, tile0 + qblock, qrb, lane, qop, sq, qsc);
 
   const int mc = tid & (D - 1);
   if (tid < D) {
@@ -329,26 +401,17 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(NW / 4, NW 
   }
   for (int e = tid; e < 2 * 2 * D * 8 / 8; e += NTH) reinterpret_cast<u4*>(&ub[0][0][0][0])[e] = u4{0, 0, 0, 0};
 
-  // row-sum operand of the 16x16x128 FP8 product: A rows 0 and 8 are ones on k-groups 0 and 2
-  // (B lanes 0..15 and 32..47: queries 0..15), rows 4 and 12 on k-groups 1 and 3 (queries
-  // 16..31); C row 4(l/16), column l%16 then holds r of query l%32 in register 0 of lane l
-  v8i ones16;
-  {
-    const int row = lane & 15, g = lane >> 4;
-    const bool on = ((row == 0 || row == 8) && !(g & 1)) || ((row == 4 || row == 12) && (g & 1));
-    const int w = on ? 0x38383838 : 0;
-    ones16 = v8i{w, w, w, w, w, w, w, w};
-  }
+  const v8i ones16 = row_sum_ones(lane);
 
   constexpr int KT_BYTES = MX ? MX_CODE_BYTES : TILE_BYTES;  // K codes per tile in memory
   const uint8_t* kbase = reinterpret_cast<const uint8_t*>(a.k) + tile0 * KT_BYTES;
   const uint8_t* ksbase = MX ? a.k_mxs + tile0 * MX_SCALE_BYTES + (MX_SCALE_BYTES / NW) * wave : nullptr;
   const uint8_t* vbase = a.v + tile0 * TILE_BYTES;
   const uint8_t* mbase = reinterpret_cast<const uint8_t*>(a.v_mean + tile0 * D) + (2 * D / NW) * wave;
-  // piece u < KCOPIES of K_t into kd (every piece one copy per wave). INT8: 1 KB of codes each;
-  // MXFP4: piece 0 = 1 KB of codes, piece 1 = MX_SCALE_BYTES / NW scale bytes
+  // piece u < KCOPIES of K_t into kd (every piece one copy per wave). INT8, FP8: 1 KB of codes each;
+  // MXFP4: the last piece is MX_SCALE_BYTES / NW scale bytes
   auto load_kpiece = [&](int u, int t, uint8_t* kd) __attribute__((always_inline)) {
-    if (!MX || u == 0) {
+    if (!MX || u < KCOPIES - 1) {
       const int off = (u * NW + wave) * 1024;
       copy16_to_lds(kbase + (size_t)t * KT_BYTES + off, lane * 16, lds_addr(kd + off));
     } else if (lane < MX_SCALE_BYTES / NW / 4) {
@@ -364,7 +427,7 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(NW / 4, NW 
   auto load_part = [&](int k, int p, uint8_t* kd, uint8_t* vd) __attribute__((always_inline)) {
     if (k < KCOPIES) {
       load_kpiece(k, min(p + 2, T - 1), kd);
-    } else if (k < 2 * KCOPIES) {
+    } else if (k < KCOPIES + VCOPIES) {
       const int off = ((k - KCOPIES) * NW + wave) * 1024;
       copy16_to_lds(vbase + (size_t)p * TILE_BYTES + off, lane * 16, lds_addr(vd + off));
     } else if (lane < MEAN_LANES) {
@@ -399,44 +462,14 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(NW / 4, NW 
   float ksc = 0.f;  // scale of the K tile whose scores are in s
   float2* rm_q = &rm[wave][0][col];   // slot t at rm_q[32 t]
 
-  // O^T += M^T R for the tiles of chunk parity `par` whose slot is <= last_slot, R_t = r_t 2^(m_t - m).
-  // k-slots 0..7 (lanes with kh = 0) carry R_hi = bf16(R), slots 8..15 (kh = 1) R_lo = bf16(R - R_hi)
-  // (R - R_hi is exact in fp32, and fma(-kh, R_hi, R) is R itself for kh = 0), against mu_hi in the
-  // first product and mu_lo in the second: the four cross terms of the two splits.
-  const float khf = (float)kh;
+  // the means of the tiles of chunk parity `par` whose slot is <= last_slot
   auto flush_means = [&](int par, int last_slot) __attribute__((always_inline)) {
-    float R[8];
-#pragma unroll
-    for (int t = 0; t < 8; ++t) {
-      const float2 e = rm_q[32 * t];
-      R[t] = t <= last_slot ? e.x * __builtin_amdgcn_exp2f(e.y - m_run) : 0.f;
-    }
-    bf16x8 b;
-#pragma unroll
-    for (int t = 0; t < 8; t += 2) {
-      const v2f hi = __builtin_convertvector(__builtin_convertvector((v2f){R[t], R[t + 1]}, bf16x2), v2f);
-      const v2f part = {__builtin_fmaf(-khf, hi[0], R[t]), __builtin_fmaf(-khf, hi[1], R[t + 1])};
-      const bf16x2 v = __builtin_convertvector(part, bf16x2);
-      b[t] = v[0];
-      b[t + 1] = v[1];
-    }
-#pragma unroll
-    for (int db = 0; db < 4; ++db) {
-      const int c = 32 * db + col;
-      const bf16x8 a_hi = *reinterpret_cast<const bf16x8*>(&ub[par][0][c][0]);
-      const bf16x8 a_lo = *reinterpret_cast<const bf16x8*>(&ub[par][1][c][0]);
-      o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a_hi, b, o[db], 0, 0, 0);
-      o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a_lo, b, o[db], 0, 0, 0);
-    }
+    add_means(o, rm_q, ub[par], last_slot, m_run, kh, col);
   };
 
   // value operand n of tile vt (A operand: residual codes, 32 channels x 64 keys; n = 4 kc + db)
   auto load_vop = [&](const uint8_t* vt, int n) __attribute__((always_inline)) -> v8i {
-    const int kc = n >> 2, db = n & 3;
-    const int base = ((((kc * 4 + db) * 2 + kh) * 2) * 32 + col) * 16;
-    const u4 lo = *reinterpret_cast<const u4*>(vt + base);
-    const u4 hi = *reinterpret_cast<const u4*>(vt + base + 512);
-    return v8i{(int)lo[0], (int)lo[1], (int)lo[2], (int)lo[3], (int)hi[0], (int)hi[1], (int)hi[2], (int)hi[3]};
+    return load_f8op(vt + (((n * 2 + kh) * 2) * 32 + col) * 16);
   };
 
   // scores of tile t (K_t in kt) into s
@@ -458,12 +491,7 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(NW / 4, NW 
   // FP8 key operands of block kb: 32 bytes per lane as two 16-byte halves 512 bytes apart
   auto f8_kops = [&](int kb, const uint8_t* kt, v8i (&k)[2]) __attribute__((always_inline)) {
 #pragma unroll
-    for (int m = 0; m < 2; ++m) {
-      const uint8_t* p = kt + ((((kb * 2 + m) * 2 + kh) * 2) * 32 + col) * 16;
-      const u4 lo = *reinterpret_cast<const u4*>(p);
-      const u4 hi = *reinterpret_cast<const u4*>(p + 512);
-      k[m] = v8i{(int)lo[0], (int)lo[1], (int)lo[2], (int)lo[3], (int)hi[0], (int)hi[1], (int)hi[2], (int)hi[3]};
-    }
+    for (int m = 0; m < 2; ++m) k[m] = load_f8op(kt + ((((kb * 2 + m) * 2 + kh) * 2) * 32 + col) * 16);
   };
 
   // scores of tile t (K_t in kt) into s
@@ -546,26 +574,18 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(NW / 4, NW 
     pin(m_run);
     pin(ksc);
   };
-  // codes of tile j (in pc) into row q of a.p_codes, dword w of chunk kc = keys 32(2kc + w/4) +
-  // 8(w%4) + 4kh .. +3; then every copy in flight and these stores complete, which leaves the
-  // copy counting of the schedule as it is
+  // codes of tile j (in pc) into a.p_codes; then every copy in flight and these stores complete,
+  // which leaves the copy counting of the schedule as it is
   const int q_dump = qt * NQ + wave * 32 + col;
   auto dump_codes = [&](int j) __attribute__((always_inline)) {
     if constexpr (DUMP) {
-      if (q_dump < a.N) {
-        uint8_t* row = a.p_codes + ((size_t)bh * a.N + q_dump) * ((size_t)T * BLK) + (size_t)j * BLK + 4 * kh;
-#pragma unroll
-        for (int kc = 0; kc < 2; ++kc)
-#pragma unroll
-          for (int w = 0; w < 8; ++w)
-            *reinterpret_cast<int*>(row + 32 * (2 * kc + (w >> 2)) + 8 * (w & 3)) = pc[kc][w];
-      }
+      if (q_dump < a.N) store_codes(a, bh, q_dump, j, kh, pc);
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     }
   };
   auto end_iter = [&](int npairs) __attribute__((always_inline)) {
     pin_state();
-    wait_pairs(npairs);
+    wait_pairs<PAIR_COPIES>(npairs);
     wg_barrier();
     pin_state();
   };
@@ -628,8 +648,12 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(NW / 4, NW 
     constexpr bool cp = decltype(COPYC)::value;
     dump_codes(j);
     __builtin_amdgcn_s_setprio(3);
-    auto hook = [&](int k) __attribute__((always_inline)) {
-      if (cp && k < PAIR_COPIES) load_part(k, j + 3, kd, vd);
+    // the pair's copies, spread over the regions
+    constexpr int PER_HOOK = (PAIR_COPIES + 4) / 5;
+    auto hook = [&](int h) __attribute__((always_inline)) {
+#pragma unroll
+      for (int k = h * PER_HOOK; k < (h + 1) * PER_HOOK; ++k)
+        if (cp && k < PAIR_COPIES) load_part(k, j + 3, kd, vd);
     };
     using E = std::remove_reference_t<decltype(s[0][0])>;
     auto kmax = [&](int kb) __attribute__((always_inline)) -> E {
@@ -775,12 +799,12 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(NW / 4, NW 
 
   // prologue: K_0, K_1, pairs 0 and 1; scores of tile 0, its codes, scores of tile 1; pair 2
   const bool t2 = T > 1, t3 = T > 2;
-  wait_pairs(0);  // the compiler's own loads have landed before any copy
+  wait_pairs<PAIR_COPIES>(0);  // the compiler's own loads have landed before any copy
   load_k(0, kb0);
   if (t2) load_k(1, kb1);
   load_pair(0, kb2, vb0);
   if (t2) load_pair(1, kb3, vb1);
-  wait_pairs(t2 ? 2 : 1);  // K_0, K_1
+  wait_pairs<PAIR_COPIES>(t2 ? 2 : 1);  // K_0, K_1
   wg_barrier();
   if (T == 1) qk(YES, 0, kb0);
   else qk(NO, 0, kb0);
@@ -862,6 +886,223 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(NW / 4, NW 
   }
 }
 
+// ------------------------------------------------------------------------------------------
+// Few queries: the keys of a 32-query group split over the eight waves of a workgroup.
+//
+// attn_fwd needs 256 queries per workgroup and one workgroup per CU, so a call with fewer than 256 x
+// 256 queries (or a last round of workgroups that is nearly empty) leaves most of the chip idle
+// while each workgroup walks all T key tiles in order. Here wave w takes tiles
+// [w T / 8, (w + 1) T / 8). The codes are defined at the running maximum over all tiles so far, so a
+// first pass forms only scores and maxima of the wave's tiles; the waves exchange them, and each
+// starts its second pass at the maximum of the tiles before its own: the codes are those of the
+// sequential walk. The waves' outputs and row sums, each at its own last running maximum, are added
+// in LDS at the final one. The first pass walks its tiles backwards, so the scores of the wave's
+// first tile are there when the second begins (up to 8 tiles no score is formed twice).
+// Tiles are read from the caches straight into registers: the operands are 16-byte pieces in lane
+// order, and no other wave of the workgroup reads the same tile.
+// ------------------------------------------------------------------------------------------
+constexpr int SPLIT = 8;
+
+template <int PMODE, int QKF, bool DUMP>
+__global__ __launch_bounds__(64 * SPLIT) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_split(FwdArgs a) {
+  constexpr bool I8 = QKF == VC_QK_INT8, F8 = QKF == VC_QK_FP8, MX = QKF == VC_QK_MXFP4;
+  using SV = std::conditional_t<I8, v16i, v16f>;
+  using QO = std::conditional_t<F8, v8i, v4i>;
+  using E = std::conditional_t<I8, int, float>;
+  // the waves' outputs; before that, per wave, mu_t / s_V as bf16 hi + lo [hi/lo][channel][slot]
+  // and (r_t, m_t) [slot][query] of up to 8 tiles
+  constexpr int MEANS = 2 * D * 8 * 2, RM = 8 * 32 * 8;
+  __shared__ __attribute__((aligned(16))) uint8_t buf[SPLIT * 64 * 64 * 4];
+  static_assert(SPLIT * (MEANS + RM) <= (int)sizeof(buf), "the mean slots fit");
+  __shared__ float mch[SPLIT][32], lsum[SPLIT][32], m_first[32];
+
+  int qt, bh, sub;
+  {
+    const int per_head = (a.N + 31) / 32;
+    const int l = a.first + xcd_order(blockIdx.x, gridDim.x);
+    bh = l / per_head;
+    qt = l - bh * per_head;
+    sub = qt & 3;
+  }
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int kh = lane >> 5, col = lane & 31;
+  const int T = a.T;
+  const size_t tile0 = (size_t)bh * T;
+  const int t0 = wave * T / SPLIT, t1 = (wave + 1) * T / SPLIT;
+
+  QO qop[I8 ? 4 : 2];
+  float sq = 1.f;
+  int qsc[2] = {0, 0};
+  load_queries<QKF>(a, tile0 + (qt >> 2), sub, lane, qop, sq, qsc);
+  const v8i ones16 = row_sum_ones(lane);
+
+  constexpr int KT_BYTES = MX ? MX_CODE_BYTES : TILE_BYTES;
+  const uint8_t* kbase = reinterpret_cast<const uint8_t*>(a.k) + tile0 * KT_BYTES;
+  const uint8_t* vbase = a.v + tile0 * TILE_BYTES;
+  SV s[4];
+  float ksc = 1.f;
+  auto scores = [&](int t) __attribute__((always_inline)) {
+    const uint8_t* kt = kbase + (size_t)t * KT_BYTES;
+    if constexpr (MX) {
+      const uint2 ksw = *reinterpret_cast<const uint2*>(a.k_mxs + (tile0 + t) * MX_SCALE_BYTES + lane * 8);
+      v4i k[4][2];
+#pragma unroll
+      for (int kb = 0; kb < 4; ++kb)
+#pragma unroll
+        for (int m = 0; m < 2; ++m) k[kb][m] = *reinterpret_cast<const v4i*>(kt + ((kb * 2 + m) * 2 + kh) * 512 + col * 16);
+      s[0] = mfma_f4<1, 0>(k[0][1], qop[1], mfma_f4<0, 0>(k[0][0], qop[0], v16f{}, (int)ksw.x, qsc[0]), (int)ksw.x, qsc[1]);
+      s[1] = mfma_f4<3, 0>(k[1][1], qop[1], mfma_f4<2, 0>(k[1][0], qop[0], v16f{}, (int)ksw.x, qsc[0]), (int)ksw.x, qsc[1]);
+      s[2] = mfma_f4<1, 0>(k[2][1], qop[1], mfma_f4<0, 0>(k[2][0], qop[0], v16f{}, (int)ksw.y, qsc[0]), (int)ksw.y, qsc[1]);
+      s[3] = mfma_f4<3, 0>(k[3][1], qop[1], mfma_f4<2, 0>(k[3][0], qop[0], v16f{}, (int)ksw.y, qsc[0]), (int)ksw.y, qsc[1]);
+    } else {
+      ksc = a.k_scale[tile0 + t];
+#pragma unroll
+      for (int kb = 0; kb < 4; ++kb) {
+        SV acc = {};
+        if constexpr (F8) {
+#pragma unroll
+          for (int m = 0; m < 2; ++m) acc = mfma_f8(load_f8op(kt + ((((kb * 2 + m) * 2 + kh) * 2) * 32 + col) * 16), qop[m], acc);
+        } else {
+#pragma unroll
+          for (int dc = 0; dc < 4; ++dc)
+            acc = mfma_i8(*reinterpret_cast<const v4i*>(kt + ((kb * 4 + dc) * 2 + kh) * 512 + col * 16), qop[dc], acc);
+        }
+        s[kb] = acc;
+      }
+    }
+    if (t == T - 1) mask_tile(s, kh, a.N - t * BLK);
+  };
+  // the running maximum m after the tile in s, and the tile's score scale
+  auto tile_max = [&](float m, float& a_s) __attribute__((always_inline)) -> float {
+    a_s = MX ? a.kappa : (sq * ksc) * a.kappa;
+    E mk[4];
+#pragma unroll
+    for (int kb = 0; kb < 4; ++kb) {
+      E v = smax(s[kb][0], s[kb][1]);
+#pragma unroll
+      for (int r = 2; r < 16; r += 2) v = smax3(v, s[kb][r], s[kb][r + 1]);
+      mk[kb] = v;
+    }
+    return fmaxf(m, (float)half_max(smax(smax(mk[0], mk[1]), smax(mk[2], mk[3]))) * a_s);
+  };
+
+  float m_run = -INFINITY, l_run = 0.f, a_s = 0.f;
+  for (int t = t1 - 1; t >= t0; --t) {
+    scores(t);
+    if (t == 0 && kh == 0) m_first[col] = tile_max(-INFINITY, a_s);   // see the epilogue
+    m_run = tile_max(m_run, a_s);
+  }
+  if (kh == 0) mch[wave][col] = m_run;
+  __syncthreads();
+  m_run = -INFINITY;
+  float m_all = -INFINITY;
+#pragma unroll
+  for (int w = 0; w < SPLIT; ++w) {
+    const float m = mch[w][col];
+    if (w < wave) m_run = fmaxf(m_run, m);
+    m_all = fmaxf(m_all, m);
+  }
+
+  v16f o[4];
+#pragma unroll
+  for (int db = 0; db < 4; ++db)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) o[db][r] = 0.f;
+  uint16_t (*ub)[D][8] = reinterpret_cast<uint16_t (*)[D][8]>(buf + wave * MEANS);
+  float2* rm_q = reinterpret_cast<float2*>(buf + SPLIT * MEANS + wave * RM) + col;
+  float inv_sv[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) inv_sv[i] = 1.f / a.v_scale[(size_t)bh * D + 64 * i + lane];
+  if (a.smooth_v)   // slots without a tile: mu = 0
+    for (int e = lane; e < MEANS / 16; e += 64) reinterpret_cast<u4*>(ub)[e] = u4{0, 0, 0, 0};
+
+  for (int t = t0; t < t1; ++t) {
+    if (t > t0) scores(t);
+    const uint8_t* vt = vbase + (size_t)t * TILE_BYTES;
+    const int slot = (t - t0) & 7;
+    const float m_new = tile_max(m_run, a_s);
+    const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+    const float mul = PMODE == 0 ? a_s * 0x1p-21f : a_s;
+    const float add = PMODE == 0 ? __builtin_fmaf(m_new, -0x1p-21f, a.cbias * 0x1p-24f) : -m_new;
+    v8i pc[2];
+#pragma unroll
+    for (int kb = 0; kb < 4; ++kb)
+#pragma unroll
+      for (int d4 = 0; d4 < 4; ++d4) pc[kb >> 1][4 * (kb & 1) + d4] = code4<PMODE>(s[kb], d4, mul, add);
+    if (PMODE == 0 && __builtin_amdgcn_ballot_w64(fabsf(m_new) >= WIDE_MAX)) clip_codes(pc);
+    if (t == T - 1) clear_padded(pc, kh, a.N - t * BLK);
+    if (DUMP && qt * 32 + col < a.N) store_codes(a, bh, qt * 32 + col, t, kh, pc);
+    if (__builtin_amdgcn_ballot_w64(alpha != 1.f)) {
+#pragma unroll
+      for (int db = 0; db < 4; ++db)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) o[db][r] *= alpha;
+      l_run *= alpha;
+    }
+    m_run = m_new;
+    v4f rs = mfma_f8_16(ones16, pc[0], v4f{});
+    rs = mfma_f8_16(ones16, pc[1], rs);
+#pragma unroll
+    for (int n = 0; n < 8; ++n) o[n & 3] = mfma_f8(load_f8op(vt + (((n * 2 + kh) * 2) * 32 + col) * 16), pc[n >> 2], o[n & 3]);
+    l_run += rs[0];
+    if (a.smooth_v) {
+      rm_q[32 * slot] = make_float2(rs[0], m_run);
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const int c = 64 * i + lane;
+        const float u = bf16_to_f32(a.v_mean[(tile0 + t) * D + c]) * inv_sv[i];
+        const uint16_t hi = f32_to_bf16(u);
+        ub[0][c][slot] = hi;
+        ub[1][c][slot] = f32_to_bf16(u - bf16_to_f32(hi));
+      }
+      if (slot == 7 || t == t1 - 1) {
+        wave_lds_sync();
+        add_means(o, rm_q, ub, slot, m_run, kh, col);
+        wave_lds_sync();
+      }
+    }
+  }
+
+  // all outputs at the last running maximum (a wave without a tile: 0 times 0)
+  const float f = __builtin_amdgcn_exp2f(m_run - m_all);
+  if (kh == 0) lsum[wave][col] = l_run * f;
+  __syncthreads();
+  float (*oall)[64][64] = reinterpret_cast<float (*)[64][64]>(buf);
+#pragma unroll
+  for (int db = 0; db < 4; ++db)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) oall[wave][16 * db + r][lane] = o[db][r] * f;
+  __syncthreads();
+  const int q = qt * 32 + col;
+  float l = 0.f;
+#pragma unroll
+  for (int w = 0; w < SPLIT; ++w) l += lsum[w][col];
+  // registers 8 wave .. + 7 of the outputs
+  float v[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    v[i] = 0.f;
+#pragma unroll
+    for (int w = 0; w < SPLIT; ++w) v[i] += oall[w][8 * wave + i][lane];
+  }
+  if (q < a.N) {
+    // a row outside the domain of the fp16 code conversion is written as NaN
+    const bool out_of_domain = PMODE == 0 && (fabsf(m_first[col]) >= DOMAIN_MAX || fabsf(m_all) >= DOMAIN_MAX);
+    const float inv_l = out_of_domain ? __builtin_nanf("") : 1.f / l;
+    const int qo = a.q_perm ? clamp_index(a.q_perm[(size_t)bh * a.N + q], a.N) : q;
+    uint16_t* orow = a.O + ((size_t)bh * a.N + qo) * D;
+#pragma unroll
+    for (int g = 0; g < 2; ++g) {
+      const int c0 = 32 * (wave >> 1) + 8 * (2 * (wave & 1) + g) + 4 * kh;
+      const float4 sv = *reinterpret_cast<const float4*>(a.v_scale + (size_t)bh * D + c0);
+      const uint32_t w0 = (uint32_t)f32_to_bf16(v[4 * g + 0] * sv.x * inv_l) | ((uint32_t)f32_to_bf16(v[4 * g + 1] * sv.y * inv_l) << 16);
+      const uint32_t w1 = (uint32_t)f32_to_bf16(v[4 * g + 2] * sv.z * inv_l) | ((uint32_t)f32_to_bf16(v[4 * g + 3] * sv.w * inv_l) << 16);
+      *reinterpret_cast<uint2*>(orow + c0) = make_uint2(w0, w1);
+    }
+  }
+}
+
 // The FP8 score product on caller data (vc_fp8_score_product): one wave per 32x32 block, the two
 // chained 32x32x64 instructions of the scores of a 32-key block (A = rows of a, B = rows of b),
 // from the accumulator c_in. Operand lane l holds row l % 32, channels 64m + 32(l / 32) .. + 31.
@@ -891,26 +1132,57 @@ hipError_t launch_fp8_score_product(const uint8_t* a, const uint8_t* b, const fl
   return hipGetLastError();
 }
 
-hipError_t launch_forward(const FwdArgs& a, int BH, hipStream_t s) {
-  const dim3 grid((a.N + NQ - 1) / NQ, BH);
-  auto go = [&](auto PC, auto DC) {
-    constexpr int pm = decltype(PC)::value;
+// How the rows are dealt out: in order of head and query, n8 workgroups of 256 queries, then n4 of
+// 128, then attn_split on groups of 32. A CU holds one workgroup of any kind, so what counts is
+// rounds of 256 workgroups times the length of a round. Measured per key tile (INT8): 256 queries
+// 1.8 us (8 waves, two per SIMD), 128 queries 1.31 us (a lone wave per SIMD waits for its own latencies),
+// attn_split 0.65 us while a head's K and V fit an XCD's L2 and 1.1 us beyond; a second launch costs
+// about 5 us. Full rounds go to the 256-query kernel; the rest, which would be a round of its own,
+// to whichever ends first. Two heads of 1024 tokens (8 workgroups before): 22.1 -> 11.5 us; one head of
+// 5850 (23): 79 -> 38; two: 82 -> 61; one of 32760 (128): 399 -> 304; 24 of 5850 (552, 2.2 rounds):
+// 276 -> 259; 7 of 13833 (385): 388 -> 350, with the exponential path 490 -> 404. The choice depends on the shape alone, so the code-dumping variant makes the same one.
+struct Plan {
+  int n8, n4;
+};
+static Plan plan(int N, int BH) {
+  constexpr int CUS = 256;
+  const int per8 = (N + 255) / 256, per4 = (N + 127) / 128, per1 = (N + 31) / 32;
+  const int T = per4, w8 = per8 * BH, full = w8 / CUS * CUS;
+  auto rounds = [](int wgs) { return (float)((wgs + CUS - 1) / CUS); };
+  if (full == w8) return {w8, 0};
+  const int u4 = BH * per4 - (full / per8 * per4 + min(full % per8 * 2, per4));   // left for the other kernels
+  const int u1 = BH * per1 - (full / per8 * per1 + min(full % per8 * 8, per1));
+  const float extra = full > 0 ? 5.f : 0.f;
+  const float t8 = 1.8f * T, t4 = rounds(u4) * 1.31f * T + extra, t1 = rounds(u1) * (N <= 16384 ? 0.7f : 1.1f) * T + extra + 1.f;
+  if (t1 < t8 && t1 < t4) return {full, 0};
+  return t4 < t8 ? Plan{full, u4} : Plan{w8, 0};
+}
+
+hipError_t launch_forward(FwdArgs a, int BH, hipStream_t s) {
+  const int per8 = (a.N + 255) / 256, per4 = (a.N + 127) / 128, per1 = (a.N + 31) / 32;
+  const auto [n8, n4] = plan(a.N, BH);
+  auto go = [&](auto PC, auto QC, auto DC) {
+    constexpr int pm = decltype(PC)::value, qf = decltype(QC)::value;
     constexpr bool dump = decltype(DC)::value;
-    if (a.qk_fmt == VC_QK_MXFP4) attn_fwd<pm, VC_QK_MXFP4, dump><<<grid, NTH, 0, s>>>(a);
-    else if (a.qk_fmt == VC_QK_FP8) attn_fwd<pm, VC_QK_FP8, dump><<<grid, NTH, 0, s>>>(a);
-    else attn_fwd<pm, VC_QK_INT8, dump><<<grid, NTH, 0, s>>>(a);
+    a.first = 0;
+    if (n8 > 0) attn_fwd<pm, qf, 8, dump><<<n8, 512, 0, s>>>(a);
+    a.first = n8 / per8 * per4 + min(n8 % per8 * 2, per4);
+    const int end4 = a.first + n4;
+    if (n4 > 0) attn_fwd<pm, qf, 4, dump><<<n4, 256, 0, s>>>(a);
+    a.first = end4 / per4 * per1 + min(end4 % per4 * 4, per1);
+    if (a.first < BH * per1) attn_split<pm, qf, dump><<<BH * per1 - a.first, 64 * SPLIT, 0, s>>>(a);
   };
-  const std::integral_constant<int, 0> EXPCAST;
-  const std::integral_constant<int, 1> EXPTHENCAST;
-  const std::integral_constant<bool, true> DUMP;
-  const std::integral_constant<bool, false> NODUMP;
-  if (a.p_codes) {
-    if (a.p_mode == 0) go(EXPCAST, DUMP);
-    else go(EXPTHENCAST, DUMP);
-  } else {
-    if (a.p_mode == 0) go(EXPCAST, NODUMP);
-    else go(EXPTHENCAST, NODUMP);
-  }
+  auto fmt = [&](auto PC, auto DC) {
+    if (a.qk_fmt == VC_QK_MXFP4) go(PC, std::integral_constant<int, VC_QK_MXFP4>{}, DC);
+    else if (a.qk_fmt == VC_QK_FP8) go(PC, std::integral_constant<int, VC_QK_FP8>{}, DC);
+    else go(PC, std::integral_constant<int, VC_QK_INT8>{}, DC);
+  };
+  auto mode = [&](auto DC) {
+    if (a.p_mode == 0) fmt(std::integral_constant<int, 0>{}, DC);
+    else fmt(std::integral_constant<int, 1>{}, DC);
+  };
+  if (a.p_codes) mode(std::integral_constant<bool, true>{});
+  else mode(std::integral_constant<bool, false>{});
   return hipGetLastError();
 }
 

@@ -46,6 +46,7 @@ struct FwdArgs {
   float cbias;      // fl(120 + beta)
   int p_mode, smooth_v;
   int qk_fmt;
+  int first;        // a launch's first workgroup (in order of head and query)
 };
 
 struct GroupArgs {
@@ -67,7 +68,7 @@ struct GroupArgs {
 };
 
 hipError_t launch_prep(const PrepArgs& a, int BH, hipStream_t s);
-hipError_t launch_forward(const FwdArgs& a, int BH, hipStream_t s);
+hipError_t launch_forward(FwdArgs a, int BH, hipStream_t s);
 hipError_t launch_group(const GroupArgs& a, int BH, hipStream_t s);
 hipError_t launch_fp8_score_product(const uint8_t* a, const uint8_t* b, const float* c_in, float* out, int n,
                                     hipStream_t s);
