@@ -1,10 +1,10 @@
 // Fused preprocessing of the 8-bit VC-Attention operands (Sec. 3.4 and Appendix B).
 //
 // Three launches per call:
-//   prep_stats    grid (ceil(T/4), B*H, 2), one wave for four blocks. z = 0: value rows of
-//                 permuted block j (gathered by perm), one pass: the block mean mu_j, stored as
-//                 bf16, and the per-channel max |V' - mu_j| of the block. z = 1: rotated key
-//                 rows of original-order block j summed per channel (the centering statistics).
+//   prep_stats    a grid over blocks, heads and z. z = 0: value rows of permuted block j (gathered by
+//                 perm), one pass: the block mean mu_j, stored as bf16, and the per-channel
+//                 max |V' - mu_j| of the block. z = 1: rotated key rows of original-order block j
+//                 summed per channel (the centering statistics).
 //   prep_finalize grid (B*H, 16), 256 threads: key channel mean and per-channel value scale.
 //   prep_quant    grid (T, B*H, 3), 256 threads. z = 0: K' rows (gather, RoPE, centering,
 //                 Hadamard, per-block INT8 or E4M3, or MXFP4); z = 1: V' rows (gather, demean,
@@ -48,24 +48,220 @@ __device__ __forceinline__ RopeRows rope_rows(int n, const PrepArgs& a) {
   return RopeRows{f, a.F + y, a.F + a.Ht + (rem - y * a.Wd)};
 }
 
-// One rotary pair with the table row of its axis: y0 = fma(x0, c, -(x1 s)), y1 = fma(x0, s, x1 c).
-__device__ __forceinline__ void rope_pair(float& x0, float& x1, int pair, const RopeRows& rr, const PrepArgs& a) {
-  const int ax = rope_axis(pair);
-  const int row = ax == 0 ? rr.f : (ax == 1 ? rr.y : rr.x);
-  const float c = a.rope_cos[row * 64 + pair], s = a.rope_sin[row * 64 + pair];
-  const float p = x1 * s, q = x1 * c;
-  const float y0 = __builtin_fmaf(x0, c, -p);
-  const float y1 = __builtin_fmaf(x0, s, q);
-  x0 = y0;
-  x1 = y1;
+// ------------------------------------------------------------------------------------------
+// A lane's part of a row: 4 lanes per row, lane k4 = lane & 3 holding the 32 channels
+// c = 32 i + 8 k4 + e (i, e = 0..3, 0..7).
+// ------------------------------------------------------------------------------------------
+__device__ __forceinline__ void load_row32(const uint16_t* row, int k4, u4 (&w)[4]) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) w[i] = *reinterpret_cast<const u4*>(row + 32 * i + 8 * k4);
+}
+__device__ __forceinline__ void unpack_row32(const u4 (&w)[4], float (&x)[4][8]) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      x[i][2 * q] = bf16_lo(w[i][q]);
+      x[i][2 * q + 1] = bf16_hi(w[i][q]);
+    }
+}
+
+// Rotary entries of a lane's pairs 16 i + 4 k4 + 0..3: one 16-byte load per table from the row of the
+// first pair's axis; the two quads that cross an axis boundary (pairs 20..23 and 40..43) patch the
+// pairs of the next axis.
+__device__ __forceinline__ void load_rope4(float4& c4, float4& s4, const RopeRows& rr, int i, int k4, const PrepArgs& a) {
+  const int p0 = 16 * i + 4 * k4;
+  const int ax0 = rope_axis(p0);
+  const int row = ax0 == 0 ? rr.f : (ax0 == 1 ? rr.y : rr.x);
+  const uint32_t o = (uint32_t)(row * 64 + p0);
+  c4 = *reinterpret_cast<const float4*>(a.rope_cos + o);
+  s4 = *reinterpret_cast<const float4*>(a.rope_sin + o);
+  if (i == 1 && k4 == 1) {
+    const uint32_t oy = (uint32_t)(rr.y * 64);
+    c4.z = a.rope_cos[oy + 22];
+    c4.w = a.rope_cos[oy + 23];
+    s4.z = a.rope_sin[oy + 22];
+    s4.w = a.rope_sin[oy + 23];
+  }
+  if (i == 2 && k4 == 2) {
+    const uint32_t ox = (uint32_t)(rr.x * 64);
+    c4.w = a.rope_cos[ox + 43];
+    s4.w = a.rope_sin[ox + 43];
+  }
+}
+__device__ __forceinline__ void rotate4(float (&x)[8], const float4& c4, const float4& s4) {
+  const float cc[4] = {c4.x, c4.y, c4.z, c4.w}, ss[4] = {s4.x, s4.y, s4.z, s4.w};
+#pragma unroll
+  for (int e = 0; e < 8; e += 2) {
+    const float x0 = x[e], x1 = x[e + 1];
+    const float pp = x1 * ss[e / 2], qq = x1 * cc[e / 2];
+    x[e] = __builtin_fmaf(x0, cc[e / 2], -pp);
+    x[e + 1] = __builtin_fmaf(x0, ss[e / 2], qq);
+  }
+}
+
+// Rotary embedding of a lane's 32 channels (16 pairs 16 i + 4 k4 + 0..3) of token n.
+__device__ __forceinline__ void rope_row32(float (&x)[4][8], int n, int k4, const PrepArgs& a) {
+  const RopeRows rr = rope_rows(n, a);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    float4 c4, s4;
+    load_rope4(c4, s4, rr, i, k4, a);
+    rotate4(x[i], c4, s4);
+  }
 }
 
 // ------------------------------------------------------------------------------------------
-// Statistics: per-block key channel sums and value block means / residual maxima.
-// A wave takes four consecutive blocks, one per 16-lane row of the wave: lane q of a row owns
-// channels 8q .. 8q + 7 (rotary pairs 4q .. 4q + 3) and walks its block's rows in ascending
-// order with 16-byte loads, so every per-channel sum is a sequential fp32 sum from 0.
+// Statistics: per-block key channel sums and value block means / residual maxima, every per-channel
+// sum a sequential fp32 sum over the block's rows in ascending order, from 0. Two kernels with the same
+// results:
+//   prep_stats_walk  a wave for four blocks, 16 lanes each, walks the rows from memory 8 or 16 at a
+//                    time: the fewest instructions and requests per byte, but each batch is one memory
+//                    latency in turn;
+//   prep_stats       a workgroup per block brings its 128 rows in with all loads in flight at once and
+//                    lays them out in LDS, where one thread per channel (keys) or per two channels
+//                    (values) forms the sums.
+// Measured (us, walk / LDS): 16 blocks (two heads of 1024 tokens) 17.1 / 6.2, 48 (six of 1000) 22 / 6.2,
+// 1104 (24 of 5850) 24.4 / 18.3, 1280 23.3 / 20.4, 3072 (12 of 32760) 41.7 / 48.8, 23640 (40 of 75600)
+// 374 / 389. Up to STATS_LDS_BLOCKS blocks the latency of the walk counts, beyond them its throughput.
 // ------------------------------------------------------------------------------------------
+constexpr int STATS_LDS_BLOCKS = 1536;
+
+// LDS word of (row, channel) of the rotated key rows: 16-byte pieces permuted by row, so that the 16
+// rows of a wave's store spread over the banks
+__device__ __forceinline__ int krow_word(int r, int c) { return r * D + (c ^ (4 * (r & 31))); }
+
+// Key statistics of block j (original order), 64 rows at a time: rotated in fp32, summed per channel.
+template <bool ROPE>
+__device__ __forceinline__ void kstats_block(const PrepArgs& a, int j, int bh, float* buf) {
+  const int tid = threadIdx.x, k4 = tid & 3, r0 = j * BLK, valid = min(BLK, a.N - r0);
+  const uint16_t* Kh = a.K + (size_t)bh * a.N * D;
+  u4 w[2][4];
+  float4 rc[4], rs[4];
+  auto load_rope = [&](int row) __attribute__((always_inline)) {
+    const RopeRows rr = rope_rows(r0 + min(row, valid - 1), a);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) load_rope4(rc[i], rs[i], rr, i, k4, a);
+  };
+#pragma unroll
+  for (int h = 0; h < 2; ++h)   // rows past the end repeat the last one and are left out of the sums
+    load_row32(Kh + (size_t)(r0 + min(64 * h + (tid >> 2), valid - 1)) * D, k4, w[h]);
+  if (ROPE) load_rope(tid >> 2);
+  // the summing waves: two of the four, by turns, so that they spread over the SIMDs
+  const int c = (tid + 128 * (j & 1)) & 255;
+  float s = 0.f;
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    float x[4][8];
+    unpack_row32(w[h], x);
+    if (ROPE)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) rotate4(x[i], rc[i], rs[i]);
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int e = 0; e < 8; e += 4)
+        *reinterpret_cast<float4*>(buf + krow_word(tid >> 2, 32 * i + 8 * k4 + e)) = make_float4(x[i][e], x[i][e + 1], x[i][e + 2], x[i][e + 3]);
+    if (ROPE && h == 0) load_rope(64 + (tid >> 2));
+    __syncthreads();
+    if (c < D) {
+      const int rows = min(64, valid - 64 * h);
+      int r = 0;
+      for (; r + 16 <= rows; r += 16) {
+        float v[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) v[u] = buf[krow_word(r + u, c)];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) s = s + v[u];
+      }
+      for (; r < rows; ++r) s = s + buf[krow_word(r, c)];
+    }
+    if (h == 0) __syncthreads();
+  }
+  if (c < D) a.ws_ksum[((size_t)bh * a.T + j) * D + c] = s;
+}
+
+// Value statistics of block j: the gathered rows, the sequential sum and the extrema of each channel.
+// With mu = bf16(sum / valid), the block's max |fl(x - mu)| is max(fl(xmax - mu), fl(mu - xmin)):
+// fl(x - mu) is monotone in x and fl(mu - x) = -fl(x - mu). One wave (by turns, so that they spread
+// over the SIMDs) forms the sums, the other three the extrema of a third of the rows each.
+__device__ __forceinline__ void vstats_block(const PrepArgs& a, int j, int bh, uint32_t* rows) {
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, r0 = j * BLK, valid = min(BLK, a.N - r0);
+  const size_t head = (size_t)bh * a.N;
+  const uint16_t* Vh = a.V + head * D + 8 * (tid & 15);
+  int n[8];
+#pragma unroll
+  for (int u = 0; u < 8; ++u) {
+    const int r = r0 + min(16 * u + (tid >> 4), valid - 1);   // rows past the end: not read below
+    n[u] = a.perm ? clamp_index(a.perm[head + r], a.N) : r;
+  }
+  u4 w[8];
+#pragma unroll
+  for (int u = 0; u < 8; ++u) w[u] = *reinterpret_cast<const u4*>(Vh + (uint32_t)n[u] * 128u);
+#pragma unroll
+  for (int u = 0; u < 8; ++u) *reinterpret_cast<u4*>(rows + (16 * u + (tid >> 4)) * 64 + 4 * (tid & 15)) = w[u];
+  __syncthreads();
+  // channels 2 lane, 2 lane + 1
+  const int role = (wave + j) & 3;
+  float s0 = 0.f, s1 = 0.f;
+  float4 e = make_float4(-__builtin_inff(), __builtin_inff(), -__builtin_inff(), __builtin_inff());   // max, min of each
+  if (role == 3) {
+    int r = 0;
+    for (; r + 16 <= valid; r += 16) {
+      uint32_t x[16];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) x[u] = rows[(r + u) * 64 + lane];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) {
+        s0 = s0 + bf16_lo(x[u]);
+        s1 = s1 + bf16_hi(x[u]);
+      }
+    }
+    for (; r < valid; ++r) {
+      const uint32_t x = rows[r * 64 + lane];
+      s0 = s0 + bf16_lo(x);
+      s1 = s1 + bf16_hi(x);
+    }
+  } else {
+    const int end = min(43 * role + 43, valid);
+#pragma unroll 8
+    for (int r = 43 * role; r < end; ++r) {
+      const uint32_t x = rows[r * 64 + lane];
+      e = make_float4(fmaxf(e.x, bf16_lo(x)), fminf(e.y, bf16_lo(x)), fmaxf(e.z, bf16_hi(x)), fminf(e.w, bf16_hi(x)));
+    }
+  }
+  __syncthreads();
+  float4 (*ext)[64] = reinterpret_cast<float4 (*)[64]>(rows);
+  if (role != 3) ext[role][lane] = e;
+  __syncthreads();
+  if (role != 3) return;
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    const float4 f = ext[i][lane];
+    e = make_float4(fmaxf(e.x, f.x), fminf(e.y, f.y), fmaxf(e.z, f.z), fminf(e.w, f.w));
+  }
+  uint16_t b0 = 0, b1 = 0;
+  if (a.smooth_v) {
+    // full blocks divide by 128 (the same value as a multiply by 2^-7)
+    b0 = f32_to_bf16(s0 / (float)valid);
+    b1 = f32_to_bf16(s1 / (float)valid);
+  }
+  const size_t o = ((size_t)bh * a.T + j) * (D / 2) + lane;
+  reinterpret_cast<uint32_t*>(a.v_mean)[o] = (uint32_t)b0 | ((uint32_t)b1 << 16);
+  const float m0 = bf16_to_f32(b0), m1 = bf16_to_f32(b1);
+  reinterpret_cast<float2*>(a.ws_vamax)[o] = make_float2(fmaxf(0.f, fmaxf(e.x - m0, m0 - e.y)), fmaxf(0.f, fmaxf(e.z - m1, m1 - e.w)));
+}
+
+// grid (T, B*H, 1 + smooth_k), 256 threads: z = 0 value statistics, z = 1 key statistics of block
+// blockIdx.x
+template <bool ROPE>
+__global__ __launch_bounds__(256, 4) void prep_stats(PrepArgs a) {
+  __shared__ __attribute__((aligned(16))) float buf[64 * D];   // 64 rotated key rows, or 128 bf16 value rows
+  if (blockIdx.z == 1)
+    kstats_block<ROPE>(a, blockIdx.x, blockIdx.y, buf);
+  else
+    vstats_block(a, blockIdx.x, blockIdx.y, reinterpret_cast<uint32_t*>(buf));
+}
 
 // Value v of lane L of the lane's 16-lane row (DPP row_newbcast), L known at compile time.
 template <int L>
@@ -109,7 +305,7 @@ __device__ __forceinline__ void unpack8(const u4& w, float (&x)[8]) {
 // the row) wraps. In a partial block the rows past the end repeat the last row and enter the
 // sums multiplied by 0 (s + (+-0) = s, as s is never -0).
 template <bool ROPE, bool FULL>
-__device__ __forceinline__ void kstats_block(const PrepArgs& a, int j, int bh, int q) {
+__device__ __forceinline__ void kstats_walk(const PrepArgs& a, int j, int bh, int q) {
   const int r0 = j * BLK;
   const int valid = FULL ? BLK : min(BLK, a.N - r0);
   const uint16_t* Kh = a.K + ((size_t)bh * a.N + r0) * D + 8 * q;
@@ -207,7 +403,7 @@ __device__ __forceinline__ void kstats_block(const PrepArgs& a, int j, int bh, i
 // the row's lanes broadcast it one row at a time. Rows past the end of a partial block repeat
 // its last row (left out of the sums, no effect on the extrema).
 template <bool FULL>
-__device__ __forceinline__ void vstats_block(const PrepArgs& a, int j, int bh, int q) {
+__device__ __forceinline__ void vstats_walk(const PrepArgs& a, int j, int bh, int q) {
   const int r0 = j * BLK;
   const int valid = FULL ? BLK : min(BLK, a.N - r0);
   const size_t head = (size_t)bh * a.N;
@@ -269,7 +465,7 @@ __device__ __forceinline__ void vstats_block(const PrepArgs& a, int j, int bh, i
 // grid (ceil(T/4), B*H, 1 + smooth_k), one wave: z = 0 value statistics, z = 1 key statistics
 // of blocks 4 blockIdx.x .. + 3 (lanes 16g .. 16g + 15 take block 4 blockIdx.x + g).
 template <bool ROPE>
-__global__ __launch_bounds__(64) void prep_stats(PrepArgs a) {
+__global__ __launch_bounds__(64) void prep_stats_walk(PrepArgs a) {
   const int g = threadIdx.x >> 4, q = threadIdx.x & 15;
   const int j = 4 * blockIdx.x + g, bh = blockIdx.y;
   // the wave's blocks are all full unless the head's last block is among them and N % 128 != 0
@@ -277,14 +473,14 @@ __global__ __launch_bounds__(64) void prep_stats(PrepArgs a) {
   if (j >= a.T) return;
   if (blockIdx.z == 1) {
     if (full)
-      kstats_block<ROPE, true>(a, j, bh, q);
+      kstats_walk<ROPE, true>(a, j, bh, q);
     else
-      kstats_block<ROPE, false>(a, j, bh, q);
+      kstats_walk<ROPE, false>(a, j, bh, q);
   } else {
     if (full)
-      vstats_block<true>(a, j, bh, q);
+      vstats_walk<true>(a, j, bh, q);
     else
-      vstats_block<false>(a, j, bh, q);
+      vstats_walk<false>(a, j, bh, q);
   }
 }
 
@@ -318,7 +514,15 @@ __global__ __launch_bounds__(256) void prep_finalize(PrepArgs a) {
     if (keys) {
       if (t < 16) {
         const float* col = reinterpret_cast<const float*>(part) + t;
-        for (int jj = 0; jj < nb; ++jj) acc = acc + col[jj * 16];
+        int jj = 0;
+        for (; jj + 32 <= nb; jj += 32) {   // the chain of additions is what takes the time: loads ahead of it
+          float v[32];
+#pragma unroll
+          for (int u = 0; u < 32; ++u) v[u] = col[(jj + u) * 16];
+#pragma unroll
+          for (int u = 0; u < 32; ++u) acc = acc + v[u];
+        }
+        for (; jj < nb; ++jj) acc = acc + col[jj * 16];
       }
     } else {
       // channel t & 15, blocks (t >> 4), (t >> 4) + 16, ...
@@ -343,8 +547,7 @@ __global__ __launch_bounds__(256) void prep_finalize(PrepArgs a) {
 }
 
 // ------------------------------------------------------------------------------------------
-// Quantization. A 128-row block per workgroup; 4 lanes per row, lane k4 = lane & 3 holding the
-// 32 channels c = 32 i + 8 k4 + e (i, e = 0..3, 0..7): the loads are 16-byte row segments and
+// Quantization. A 128-row block per workgroup, 4 lanes per row: the loads are 16-byte row segments and
 // the 128-point Walsh-Hadamard transform needs only two cross-lane stages (channel bits 3, 4).
 // ------------------------------------------------------------------------------------------
 __device__ __forceinline__ float wave_max(float v) {
@@ -412,54 +615,6 @@ __device__ __forceinline__ void fwht_rows(float (&x)[4][8], int k4) {
         }
 }
 
-__device__ __forceinline__ void load_row32(const uint16_t* row, int k4, float (&x)[4][8]) {
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const u4 w = *reinterpret_cast<const u4*>(row + 32 * i + 8 * k4);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      x[i][2 * q] = bf16_lo(w[q]);
-      x[i][2 * q + 1] = bf16_hi(w[q]);
-    }
-  }
-}
-
-// Rotary embedding of a lane's 32 channels (16 pairs 16 i + 4 k4 + 0..3) of token n.
-__device__ __forceinline__ void rope_row32(float (&x)[4][8], int n, int k4, const PrepArgs& a) {
-  const RopeRows rr = rope_rows(n, a);
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    // one 16-byte load per table from the row of the first pair's axis; the two quads that
-    // cross an axis boundary (pairs 20..23 and 40..43) patch the pairs of the next axis
-    const int p0 = 16 * i + 4 * k4;
-    const int ax0 = rope_axis(p0);
-    const int row = ax0 == 0 ? rr.f : (ax0 == 1 ? rr.y : rr.x);
-    const uint32_t o = (uint32_t)(row * 64 + p0);
-    float4 c4 = *reinterpret_cast<const float4*>(a.rope_cos + o);
-    float4 s4 = *reinterpret_cast<const float4*>(a.rope_sin + o);
-    if (i == 1 && k4 == 1) {
-      const uint32_t oy = (uint32_t)(rr.y * 64);
-      c4.z = a.rope_cos[oy + 22];
-      c4.w = a.rope_cos[oy + 23];
-      s4.z = a.rope_sin[oy + 22];
-      s4.w = a.rope_sin[oy + 23];
-    }
-    if (i == 2 && k4 == 2) {
-      const uint32_t ox = (uint32_t)(rr.x * 64);
-      c4.w = a.rope_cos[ox + 43];
-      s4.w = a.rope_sin[ox + 43];
-    }
-    const float cc[4] = {c4.x, c4.y, c4.z, c4.w}, ss[4] = {s4.x, s4.y, s4.z, s4.w};
-#pragma unroll
-    for (int e = 0; e < 8; e += 2) {
-      const float x0 = x[i][e], x1 = x[i][e + 1];
-      const float pp = x1 * ss[e / 2], qq = x1 * cc[e / 2];
-      x[i][e] = __builtin_fmaf(x0, cc[e / 2], -pp);
-      x[i][e + 1] = __builtin_fmaf(x0, ss[e / 2], qq);
-    }
-  }
-}
-
 // Nearest E2M1 (MX FP4) code of v, |v| < 8: ties to the code with mantissa bit 0, saturating at
 // 6, +0 for magnitudes that round to 0. With a = |v|, the code magnitude is rint(2a) below 2,
 // 4 + rint(a - 2) on [2, 4) and 6 + rint((a - 4) / 2) on [4, 8) (each argument exact, so rint's
@@ -493,7 +648,9 @@ __device__ __forceinline__ void quant_qk(const PrepArgs& a, float* red, uint8_t*
     const int row = r0 + wave * 32 + it * 16 + (lane >> 2);
     valid[it] = row < a.N;
     const int n = valid[it] ? (gather ? clamp_index(gather[row], a.N) : row) : 0;
-    load_row32(X + (head + n) * D, k4, x[it]);
+    u4 w[4];
+    load_row32(X + (head + n) * D, k4, w);
+    unpack_row32(w, x[it]);
     if (ROPE) rope_row32(x[it], n, k4, a);
     if (IS_K) {
       // the key mean (zeros without centering: x - 0 = x)
@@ -628,8 +785,10 @@ __device__ __forceinline__ void quant_v(const PrepArgs& a, uint8_t (*vt)[D + 8])
     const int row = r0 + rl;
     const bool valid = row < a.N;
     const int n = valid ? (gather ? clamp_index(gather[row], a.N) : row) : 0;
+    u4 w[4];
     float x[4][8];
-    load_row32(a.V + (head + n) * D, k4, x);
+    load_row32(a.V + (head + n) * D, k4, w);
+    unpack_row32(w, x);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const u4 mw = *reinterpret_cast<const u4*>(mu + 32 * i);
@@ -683,11 +842,16 @@ __global__ __launch_bounds__(256) void prep_quant(PrepArgs a) {
 }
 
 hipError_t launch_prep(const PrepArgs& a, int BH, hipStream_t s) {
-  const dim3 sgrid((a.T + 3) / 4, BH, a.smooth_k ? 2 : 1);
-  if (a.rope)
-    prep_stats<true><<<sgrid, 64, 0, s>>>(a);
+  const bool lds = (long long)a.T * BH <= STATS_LDS_BLOCKS;
+  const dim3 sgrid(lds ? a.T : (a.T + 3) / 4, BH, a.smooth_k ? 2 : 1);
+  if (lds && a.rope)
+    prep_stats<true><<<sgrid, 256, 0, s>>>(a);
+  else if (lds)
+    prep_stats<false><<<sgrid, 256, 0, s>>>(a);
+  else if (a.rope)
+    prep_stats_walk<true><<<sgrid, 64, 0, s>>>(a);
   else
-    prep_stats<false><<<sgrid, 64, 0, s>>>(a);
+    prep_stats_walk<false><<<sgrid, 64, 0, s>>>(a);
   prep_finalize<<<dim3(BH, 16), 256, 0, s>>>(a);
   const dim3 grid(a.T, BH, 3);
   auto quant = [&](auto QFC) {

@@ -1,0 +1,46 @@
+"""The two statistics kernels of the preprocessing on both sides of the line between them (1536 blocks of
+128 rows over all heads): codes, scales and means of the first, a middle and the last head bit for bit
+against the CPU oracle, ragged last blocks, with and without permutation, rotation and centering."""
+import numpy as np
+import pytest
+
+import oracle
+import synthetic as S
+from layouts import untile_qk, untile_v
+from test_gpu_mx import rand_qkv
+from test_gpu_parity import assert_prep_equal, dev16, dev32
+
+torch = pytest.importorskip("torch")
+vc = pytest.importorskip("paper_2609_15810_amd")
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _need_gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    vc.lib()
+
+
+@pytest.mark.parametrize("H", [768, 772])   # 1536 blocks; 1544 blocks, waves of four with one or two blocks
+@pytest.mark.parametrize("grid,perm,opt", [
+    ((2, 9, 11), True, {}),                                     # N = 198: rows wrap within a batch, ragged block
+    ((1, 1, 129), True, dict(smooth_v=False)),                  # a last block of one row
+    ((16, 16, 1), False, dict(smooth_k=False)),                 # full blocks, one column per row
+    ((2, 16, 8), False, dict(rope=False, hadamard=False)),
+])
+def test_both_sides_of_the_line(H, grid, perm, opt):
+    N = grid[0] * grid[1] * grid[2]
+    sel = [0, H // 2, H - 1]
+    Qs, Ks, Vs = rand_qkv(1, 3, N, N + len(opt))
+    ps = S.random_perm(N, N, 1, 3)
+    full = lambda x: np.concatenate([x[:, :1], np.repeat(x[:, 1:2], H - 2, 1), x[:, 2:]], 1)   # heads 1 .. H - 2 alike
+    A = vc.Attention(1, H, grid, vc.make_opts(**opt), vc.make_group_opts(mode=vc.GROUP_IDENTITY))
+    A.prep(dev16(full(Qs)), dev16(full(Ks)), dev16(full(Vs)), perm=dev32(full(ps)) if perm else None)
+    torch.cuda.synchronize()
+    P = A.prepped
+    pick = lambda t: t[:, sel].contiguous().cpu().numpy()
+    got = dict(q=untile_qk(pick(P.q)), q_scale=pick(P.q_scale), k=untile_qk(pick(P.k)), k_scale=pick(P.k_scale),
+               k_mean=pick(P.k_mean), v=untile_v(pick(P.v)), v_scale=pick(P.v_scale), v_mean=pick(P.v_mean).view(np.uint16))
+    assert_prep_equal(got, oracle.prep(Qs, Ks, Vs, grid, perm=ps if perm else None, **opt), f"H={H} {grid}")
