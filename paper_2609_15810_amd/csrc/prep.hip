@@ -615,16 +615,18 @@ __device__ __forceinline__ void fwht_rows(float (&x)[4][8], int k4) {
         }
 }
 
-// Nearest E2M1 (MX FP4) code of v, |v| < 8: ties to the code with mantissa bit 0, saturating at
-// 6, +0 for magnitudes that round to 0. With a = |v|, the code magnitude is rint(2a) below 2,
-// 4 + rint(a - 2) on [2, 4) and 6 + rint((a - 4) / 2) on [4, 8) (each argument exact, so rint's
-// ties to even are the format's ties), capped at 7.
-__device__ __forceinline__ uint32_t fp4_code(float v) {
-  const float a = fabsf(v);
-  const float t = a < 2.f ? 2.f * a : (a < 4.f ? a - 2.f : __builtin_fmaf(a, 0.5f, -2.f));
-  const float base = a < 2.f ? 0.f : (a < 4.f ? 4.f : 6.f);
-  const uint32_t mag = (uint32_t)fminf(base + __builtin_rintf(t), 7.f);
-  return mag | ((v < 0.f && mag != 0u) ? 8u : 0u);
+// Nearest E2M1 (MX FP4) codes of eight values, |v| < 8, one per nibble: the hardware conversion (ties
+// to the code with mantissa bit 0, saturating at 6; scale 1), with +0 for magnitudes that round to 0.
+// NaN becomes +6 (fminf(NaN, 7) = 7).
+__device__ __forceinline__ uint32_t fp4_codes(const float (&v)[8], float mult) {
+  uint32_t w = 0;
+  auto at = [&](int e) __attribute__((always_inline)) { return fminf(v[e] * mult, 7.f); };
+  w = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(w, at(0), at(1), 1.f, 0);
+  w = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(w, at(2), at(3), 1.f, 1);
+  w = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(w, at(4), at(5), 1.f, 2);
+  w = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(w, at(6), at(7), 1.f, 3);
+  const uint32_t mag = w & 0x77777777u;
+  return mag | (w & (mag + 0x77777777u) & 0x88888888u);
 }
 
 // Q (IS_K = false) or K' (IS_K = true) rows of block j: gather, RoPE, centering (K), Hadamard,
@@ -692,9 +694,7 @@ __device__ __forceinline__ void quant_qk(const PrepArgs& a, float* red, uint8_t*
         const int sb = m > 0.f ? max(ef - 2, 0) : 127;
         // sigma * 2^-X (exact scaling; the carried Hadamard sign restored)
         const float mult = sigma * __uint_as_float((uint32_t)(254 - sb) << 23);
-        uint32_t w = 0;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) w |= fp4_code(x[it][i][e] * mult) << (4 * e);
+        const uint32_t w = fp4_codes(x[it][i], mult);
         const int mm = i >> 1, hh = i & 1;
         *reinterpret_cast<uint32_t*>(codes + ((rb * 2 + mm) * 2 + hh) * 512 + r * 16 + 4 * k4) = w;
         if (k4 == 0) stage[(hh * 32 + r) * 8 + rb * 2 + mm] = (uint8_t)sb;
