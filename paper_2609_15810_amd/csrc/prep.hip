@@ -303,7 +303,7 @@ __device__ __forceinline__ void unpack8(const u4& w, float (&x)[8]) {
 // for q = 5, pairs 20..23 straddling frames/rows, and q = 10, pairs 40..43 straddling
 // rows/columns). Both byte offsets move by lane constants per token and when the column (then
 // the row) wraps. In a partial block the rows past the end repeat the last row and enter the
-// sums multiplied by 0 (s + (+-0) = s, as s is never -0).
+// sums as 0 (s + 0 = s, as s is never -0).
 template <bool ROPE, bool FULL>
 __device__ __forceinline__ void kstats_walk(const PrepArgs& a, int j, int bh, int q) {
   const int r0 = j * BLK;
@@ -383,9 +383,8 @@ __device__ __forceinline__ void kstats_walk(const PrepArgs& a, int j, int bh, in
         }
       }
       if (!FULL) {
-        const float keep = r + u < valid ? 1.f : 0.f;
 #pragma unroll
-        for (int c = 0; c < 8; ++c) v[c] = v[c] * keep;
+        for (int c = 0; c < 8; ++c) v[c] = r + u < valid ? v[c] : 0.f;
       }
 #pragma unroll
       for (int c = 0; c < 8; ++c) s[c] = s[c] + v[c];
@@ -430,10 +429,9 @@ __device__ __forceinline__ void vstats_walk(const PrepArgs& a, int j, int bh, in
     for (int u = 0; u < 16; ++u) {
       float v[8];
       unpack8(w[u], v);
-      const float keep = (FULL || r + u < valid) ? 1.f : 0.f;
 #pragma unroll
       for (int c = 0; c < 8; ++c) {
-        s[c] = s[c] + (FULL ? v[c] : v[c] * keep);
+        s[c] = s[c] + (FULL || r + u < valid ? v[c] : 0.f);
         hi[c] = fmaxf(hi[c], v[c]);
         lo[c] = fminf(lo[c], v[c]);
       }

@@ -44,3 +44,19 @@ def test_both_sides_of_the_line(H, grid, perm, opt):
     got = dict(q=untile_qk(pick(P.q)), q_scale=pick(P.q_scale), k=untile_qk(pick(P.k)), k_scale=pick(P.k_scale),
                k_mean=pick(P.k_mean), v=untile_v(pick(P.v)), v_scale=pick(P.v_scale), v_mean=pick(P.v_mean).view(np.uint16))
     assert_prep_equal(got, oracle.prep(Qs, Ks, Vs, grid, perm=ps if perm else None, **opt), f"H={H} {grid}")
+
+
+@pytest.mark.parametrize("H", [2, 800])
+def test_infinity_in_the_last_row_of_a_ragged_block(H):
+    """The rows that pad a ragged block repeat its last row and stay out of its sums, whatever they hold."""
+    N, grid = 198, (2, 9, 11)
+    V = np.repeat(rand_qkv(1, 1, N, 5)[2], H, 1)
+    V[0, :, N - 1, 3] = 0x7f80   # +inf
+    Q, K = np.zeros_like(V), np.zeros_like(V)
+    A = vc.Attention(1, H, grid, vc.make_opts(), vc.make_group_opts(mode=vc.GROUP_IDENTITY))
+    A.prep(dev16(Q), dev16(K), dev16(V), perm=None)
+    torch.cuda.synchronize()
+    m = A.prepped.v_mean.cpu().numpy().view(np.uint16)
+    o = oracle.prep(Q[:, :1], K[:, :1], V[:, :1], grid)["v_mean"]
+    assert o[0, 0, 1, 3] == 0x7f80
+    assert all(np.array_equal(m[0, h], o[0, 0]) for h in range(H))
