@@ -627,12 +627,28 @@ __device__ __forceinline__ uint32_t fp4_codes(const float (&v)[8], float mult) {
   return mag | (w & (mag + 0x77777777u) & 0x88888888u);
 }
 
+// Codes of calls with more than STREAM_BLOCKS blocks (over 75 MB) are stored past the caches (NT): kept in
+// them they push out K and V rows that the statistics just read and that are read again here, and
+// they would be gone themselves before the attention gets to them. Smaller calls keep them for the
+// attention. Measured (us, whole preprocessing, kept / past the caches): 12 heads of 32760 tokens 131.5 /
+// 120.9, 20 236.9 / 217.8, 40 of 75600 1080 / 1042, 24 of 12150 (2280 blocks) 100.6 / 90.0, 6 of 32760
+// (1536) 69.5 / 68.0, 24 of 5850 (1104) 52.1 / 51.5 with an attention 2 us longer. Loads past the caches
+// (1081 -> 1110 us at 40 x 75600) and heads walked backwards (no change) did not help.
+constexpr int STREAM_BLOCKS = 1536;
+template <bool NT, typename V>
+__device__ __forceinline__ void store_codes(void* p, V v) {
+  if constexpr (NT)
+    __builtin_nontemporal_store(v, reinterpret_cast<V*>(p));
+  else
+    *reinterpret_cast<V*>(p) = v;
+}
+
 // Q (IS_K = false) or K' (IS_K = true) rows of block j: gather, RoPE, centering (K), Hadamard,
 // then, by the format QF: per-block symmetric INT8 (VC_QK_INT8: scale = amax/127, code =
 // rint(x * (127/amax))), per-block symmetric E4M3 (VC_QK_FP8: scale = amax/448, code = the
 // nearest-even E4M3 of x * (448/amax), +0 for codes of zero magnitude) or MXFP4 by 32-channel
 // blocks (VC_QK_MXFP4: E8M0 scale byte floor(log2(amax)) - 2 + 127 per block).
-template <bool IS_K, bool ROPE, bool HAD, int QF>
+template <bool IS_K, bool ROPE, bool HAD, int QF, bool NT>
 __device__ __forceinline__ void quant_qk(const PrepArgs& a, float* red, uint8_t* stage) {
   const int j = blockIdx.x, bh = blockIdx.y;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, k4 = lane & 3;
@@ -694,7 +710,7 @@ __device__ __forceinline__ void quant_qk(const PrepArgs& a, float* red, uint8_t*
         const float mult = sigma * __uint_as_float((uint32_t)(254 - sb) << 23);
         const uint32_t w = fp4_codes(x[it][i], mult);
         const int mm = i >> 1, hh = i & 1;
-        *reinterpret_cast<uint32_t*>(codes + ((rb * 2 + mm) * 2 + hh) * 512 + r * 16 + 4 * k4) = w;
+        store_codes<NT>(codes + ((rb * 2 + mm) * 2 + hh) * 512 + r * 16 + 4 * k4, w);
         if (k4 == 0) stage[(hh * 32 + r) * 8 + rb * 2 + mm] = (uint8_t)sb;
       }
     }
@@ -741,7 +757,7 @@ __device__ __forceinline__ void quant_qk(const PrepArgs& a, float* red, uint8_t*
           w[u] = v & (((t + 0x7f7f7f7fu) & 0x80808080u) | 0x7f7f7f7fu);
         }
         const int off = ((((rb * 2 + (i >> 1)) * 2 + (i & 1)) * 2 + (k4 >> 1)) * 32 + r) * 16 + 8 * (k4 & 1);
-        *reinterpret_cast<uint2*>(codes + off) = make_uint2(w[0], w[1]);
+        store_codes<NT>(codes + off, u2{w[0], w[1]});
       }
     }
     return;
@@ -762,13 +778,14 @@ __device__ __forceinline__ void quant_qk(const PrepArgs& a, float* red, uint8_t*
       for (int e = 0; e < 8; ++e) b[e] = __float_as_uint(x[it][i][e] * mult + 12582912.f);
       const uint32_t lo = __builtin_amdgcn_perm(b[1], b[0], 0x0c0c0400u) | __builtin_amdgcn_perm(b[3], b[2], 0x04000c0cu);
       const uint32_t hi = __builtin_amdgcn_perm(b[5], b[4], 0x0c0c0400u) | __builtin_amdgcn_perm(b[7], b[6], 0x04000c0cu);
-      *reinterpret_cast<uint2*>(codes + qk_tile_offset(rl, 32 * i + 8 * k4)) = make_uint2(lo, hi);
+      store_codes<NT>(codes + qk_tile_offset(rl, 32 * i + 8 * k4), u2{lo, hi});
     }
   }
 }
 
 // V' rows of block j: gather, subtract the block mean (bf16; zeros without demeaning), scale per
 // channel, E4M3 RNE, transposed through LDS into the tile order of the attention kernel.
+template <bool NT>
 __device__ __forceinline__ void quant_v(const PrepArgs& a, uint8_t (*vt)[D + 8]) {
   const int j = blockIdx.x, bh = blockIdx.y;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, k4 = lane & 3;
@@ -820,23 +837,23 @@ __device__ __forceinline__ void quant_v(const PrepArgs& a, uint8_t (*vt)[D + 8])
       const int key = 32 * (2 * kc + sh) + 8 * (t >> 2) + 4 * kh + (t & 3);
       w[t >> 2] |= (uint32_t)vt[key][ch] << (8 * (t & 3));
     }
-    *reinterpret_cast<u4*>(codes + (size_t)chunk * 16) = u4{w[0], w[1], w[2], w[3]};
+    store_codes<NT>(codes + (size_t)chunk * 16, u4{w[0], w[1], w[2], w[3]});
   }
 }
 
 // grid (T, B*H, 3): z = 0 K' rows, z = 1 V' rows, z = 2 Q rows of block blockIdx.x.
-template <bool ROPE, bool HAD, int QF>
+template <bool ROPE, bool HAD, int QF, bool NT>
 __global__ __launch_bounds__(256) void prep_quant(PrepArgs a) {
   __shared__ float red[4];
   // V codes of the block, row-major (8-byte rows), for the transpose; MX scale bytes of a Q/K block
   __shared__ uint8_t vt[BLK][D + 8];
   // K' and V' first: their rows were just read by the statistics pass and may still be cached
   if (blockIdx.z == 0)
-    quant_qk<true, ROPE, HAD, QF>(a, red, &vt[0][0]);
+    quant_qk<true, ROPE, HAD, QF, NT>(a, red, &vt[0][0]);
   else if (blockIdx.z == 1)
-    quant_v(a, vt);
+    quant_v<NT>(a, vt);
   else
-    quant_qk<false, ROPE, HAD, QF>(a, red, &vt[0][0]);
+    quant_qk<false, ROPE, HAD, QF, NT>(a, red, &vt[0][0]);
 }
 
 hipError_t launch_prep(const PrepArgs& a, int BH, hipStream_t s) {
@@ -852,26 +869,33 @@ hipError_t launch_prep(const PrepArgs& a, int BH, hipStream_t s) {
     prep_stats_walk<false><<<sgrid, 64, 0, s>>>(a);
   prep_finalize<<<dim3(BH, 16), 256, 0, s>>>(a);
   const dim3 grid(a.T, BH, 3);
-  auto quant = [&](auto QFC) {
+  auto quant = [&](auto QFC, auto NTC) {
     constexpr int qf = decltype(QFC)::value;
+    constexpr bool nt = decltype(NTC)::value;
     if (a.rope) {
       if (a.hadamard)
-        prep_quant<true, true, qf><<<grid, 256, 0, s>>>(a);
+        prep_quant<true, true, qf, nt><<<grid, 256, 0, s>>>(a);
       else
-        prep_quant<true, false, qf><<<grid, 256, 0, s>>>(a);
+        prep_quant<true, false, qf, nt><<<grid, 256, 0, s>>>(a);
     } else {
       if (a.hadamard)
-        prep_quant<false, true, qf><<<grid, 256, 0, s>>>(a);
+        prep_quant<false, true, qf, nt><<<grid, 256, 0, s>>>(a);
       else
-        prep_quant<false, false, qf><<<grid, 256, 0, s>>>(a);
+        prep_quant<false, false, qf, nt><<<grid, 256, 0, s>>>(a);
     }
   };
-  if (a.qk_fmt == VC_QK_MXFP4)
-    quant(std::integral_constant<int, VC_QK_MXFP4>{});
-  else if (a.qk_fmt == VC_QK_FP8)
-    quant(std::integral_constant<int, VC_QK_FP8>{});
+  auto format = [&](auto NTC) {
+    if (a.qk_fmt == VC_QK_MXFP4)
+      quant(std::integral_constant<int, VC_QK_MXFP4>{}, NTC);
+    else if (a.qk_fmt == VC_QK_FP8)
+      quant(std::integral_constant<int, VC_QK_FP8>{}, NTC);
+    else
+      quant(std::integral_constant<int, VC_QK_INT8>{}, NTC);
+  };
+  if ((long long)a.T * BH > STREAM_BLOCKS)
+    format(std::integral_constant<bool, true>{});
   else
-    quant(std::integral_constant<int, VC_QK_INT8>{});
+    format(std::integral_constant<bool, false>{});
   return hipGetLastError();
 }
 

@@ -1,5 +1,5 @@
-"""The two statistics kernels of the preprocessing on both sides of the line between them (1536 blocks of
-128 rows over all heads): codes, scales and means of the first, a middle and the last head bit for bit
+"""The two statistics kernels of the preprocessing and the two ways of storing codes on both sides of the
+line between them (1536 blocks of 128 rows over all heads): codes, scales and means of the first, a middle and the last head bit for bit
 against the CPU oracle, ragged last blocks, with and without permutation, rotation and centering."""
 import numpy as np
 import pytest
@@ -23,7 +23,7 @@ def _need_gpu():
     vc.lib()
 
 
-@pytest.mark.parametrize("H", [768, 772])   # 1536 blocks; 1544 blocks, waves of four with one or two blocks
+@pytest.mark.parametrize("H", [768, 772])   # 1536 blocks; 1544, waves of four blocks with one or two of them past the end
 @pytest.mark.parametrize("grid,perm,opt", [
     ((2, 9, 11), True, {}),                                     # N = 198: rows wrap within a batch, ragged block
     ((1, 1, 129), True, dict(smooth_v=False)),                  # a last block of one row
@@ -44,6 +44,30 @@ def test_both_sides_of_the_line(H, grid, perm, opt):
     got = dict(q=untile_qk(pick(P.q)), q_scale=pick(P.q_scale), k=untile_qk(pick(P.k)), k_scale=pick(P.k_scale),
                k_mean=pick(P.k_mean), v=untile_v(pick(P.v)), v_scale=pick(P.v_scale), v_mean=pick(P.v_mean).view(np.uint16))
     assert_prep_equal(got, oracle.prep(Qs, Ks, Vs, grid, perm=ps if perm else None, **opt), f"H={H} {grid}")
+
+
+@pytest.mark.parametrize("fmt", ["fp8", "mxfp4"])
+def test_score_formats_past_the_line(fmt):
+    from layouts import untile_f8, untile_mx_codes, untile_mx_scales
+    H, N, grid = 800, 198, (2, 9, 11)
+    sel = [0, 400, 799]
+    Qs, Ks, Vs = rand_qkv(1, 3, N, 77)
+    full = lambda x: np.concatenate([x[:, :1], np.repeat(x[:, 1:2], H - 2, 1), x[:, 2:]], 1)
+    A = vc.Attention(1, H, grid, vc.make_opts(qk_fmt={"fp8": vc.QK_FP8, "mxfp4": vc.QK_MXFP4}[fmt]),
+                     vc.make_group_opts(mode=vc.GROUP_IDENTITY))
+    A.prep(dev16(full(Qs)), dev16(full(Ks)), dev16(full(Vs)), perm=None)
+    torch.cuda.synchronize()
+    P = A.prepped
+    u8 = lambda t: t[:, sel].contiguous().cpu().numpy().view(np.uint8)
+    o = oracle.prep(Qs, Ks, Vs, grid, qk_fmt={"fp8": oracle.QK_FP8, "mxfp4": oracle.QK_MXFP4}[fmt])
+    if fmt == "fp8":
+        pairs = [(untile_f8(u8(P.q)), o["q"].view(np.uint8)), (untile_f8(u8(P.k)), o["k"].view(np.uint8))]
+    else:
+        pairs = [(untile_mx_codes(u8(P.q)), o["q_mx"]), (untile_mx_scales(u8(P.q_mx_scale)), o["q_mxs"]),
+                 (untile_mx_codes(u8(P.k)), o["k_mx"]), (untile_mx_scales(u8(P.k_mx_scale)), o["k_mxs"])]
+    pairs.append((untile_v(u8(P.v)), o["v"]))
+    for i, (g, r) in enumerate(pairs):
+        assert np.array_equal(g, r), (fmt, i)
 
 
 @pytest.mark.parametrize("H", [2, 800])
