@@ -123,9 +123,10 @@ __device__ __forceinline__ void rope_row32(float (&x)[4][8], int n, int k4, cons
 //                    (values) forms the sums.
 // Measured (us, walk / LDS): 16 blocks (two heads of 1024 tokens) 17.1 / 6.2, 48 (six of 1000) 22 / 6.2,
 // 1104 (24 of 5850) 24.4 / 18.3, 1280 23.3 / 20.4, 3072 (12 of 32760) 41.7 / 48.8, 23640 (40 of 75600)
-// 374 / 389. Up to STATS_LDS_BLOCKS blocks the latency of the walk counts, beyond them its throughput.
+// 374 / 389; whole preprocessing at 1330 blocks 61.9 / 62.3, at 1536 67.1 / 69.3. Up to STATS_LDS_BLOCKS
+// blocks the latency of the walk counts, beyond them its throughput.
 // ------------------------------------------------------------------------------------------
-constexpr int STATS_LDS_BLOCKS = 1536;
+constexpr int STATS_LDS_BLOCKS = 1280;
 
 // LDS word of (row, channel) of the rotated key rows: 16-byte pieces permuted by row, so that the 16
 // rows of a wave's store spread over the banks
@@ -627,14 +628,14 @@ __device__ __forceinline__ uint32_t fp4_codes(const float (&v)[8], float mult) {
   return mag | (w & (mag + 0x77777777u) & 0x88888888u);
 }
 
-// Codes of calls with more than STREAM_BLOCKS blocks (over 75 MB) are stored past the caches (NT): kept in
+// Codes of calls with more than STREAM_BLOCKS blocks (over 60 MB) are stored past the caches (NT): kept in
 // them they push out K and V rows that the statistics just read and that are read again here, and
 // they would be gone themselves before the attention gets to them. Smaller calls keep them for the
 // attention. Measured (us, whole preprocessing, kept / past the caches): 12 heads of 32760 tokens 131.5 /
 // 120.9, 20 236.9 / 217.8, 40 of 75600 1080 / 1042, 24 of 12150 (2280 blocks) 100.6 / 90.0, 6 of 32760
-// (1536) 69.5 / 68.0, 24 of 5850 (1104) 52.1 / 51.5 with an attention 2 us longer. Loads past the caches
+// (1536) 68.2 / 67.1, 24 of 5850 (1104) 52.1 / 51.5 with an attention 2 us longer. Loads past the caches
 // (1081 -> 1110 us at 40 x 75600) and heads walked backwards (no change) did not help.
-constexpr int STREAM_BLOCKS = 1536;
+constexpr int STREAM_BLOCKS = 1280;
 template <bool NT, typename V>
 __device__ __forceinline__ void store_codes(void* p, V v) {
   if constexpr (NT)

@@ -1,5 +1,5 @@
 """The two statistics kernels of the preprocessing and the two ways of storing codes on both sides of the
-line between them (1536 blocks of 128 rows over all heads): codes, scales and means of the first, a middle and the last head bit for bit
+line between them (1280 blocks of 128 rows over all heads): codes, scales and means of the first, a middle and the last head bit for bit
 against the CPU oracle, ragged last blocks, with and without permutation, rotation and centering."""
 import numpy as np
 import pytest
@@ -23,7 +23,7 @@ def _need_gpu():
     vc.lib()
 
 
-@pytest.mark.parametrize("H", [768, 772])   # 1536 blocks; 1544, waves of four blocks with one or two of them past the end
+@pytest.mark.parametrize("H", [640, 644])   # 1280 blocks; 1288, waves of four blocks with one or two of them past the end
 @pytest.mark.parametrize("grid,perm,opt", [
     ((2, 9, 11), True, {}),                                     # N = 198: rows wrap within a batch, ragged block
     ((1, 1, 129), True, dict(smooth_v=False)),                  # a last block of one row
