@@ -1,11 +1,12 @@
 // Fused preprocessing of the 8-bit VC-Attention operands (Sec. 3.4 and Appendix B).
 //
-// Three launches per call:
+// Two or three launches per call:
 //   prep_stats    a grid over blocks, heads and z. z = 0: value rows of permuted block j (gathered by
 //                 perm), one pass: the block mean mu_j, stored as bf16, and the per-channel
 //                 max |V' - mu_j| of the block. z = 1: rotated key rows of original-order block j
 //                 summed per channel (the centering statistics).
-//   prep_finalize grid (B*H, 16), 256 threads: key channel mean and per-channel value scale.
+//   prep_finalize grid (B*H, 16), 256 threads: key channel mean and per-channel value scale (calls with few
+//                 blocks per head fold it into prep_quant).
 //   prep_quant    grid (T, B*H, 3), 256 threads. z = 0: K' rows (gather, RoPE, centering,
 //                 Hadamard, per-block INT8 or E4M3, or MXFP4); z = 1: V' rows (gather, demean,
 //                 per-channel E4M3), transposed into the tile order of the attention kernel;
@@ -636,6 +637,25 @@ __device__ __forceinline__ uint32_t fp4_codes(const float (&v)[8], float mult) {
 // (1536) 68.2 / 67.1, 24 of 5850 (1104) 52.1 / 51.5 with an attention 2 us longer. Loads past the caches
 // (1081 -> 1110 us at 40 x 75600) and heads walked backwards (no change) did not help.
 constexpr int STREAM_BLOCKS = 1280;
+// How a call's codes and head statistics are handled: FOLD (up to FOLD_BLOCKS blocks per head, and cached
+// stores): every workgroup forms its head's key mean or value scales from the block partials itself,
+// in the order of prep_finalize, which saves that launch and its 3 us (whole preprocessing of six heads
+// of 1000 tokens 14.5 -> 12.6 us). KEEP and STREAM read them; with more blocks per head every workgroup
+// would read more partials than rows.
+enum QuantMode { FOLD, KEEP, STREAM };
+constexpr int FOLD_BLOCKS = 16;
+
+// Channel c's partials of the head's T <= FOLD_BLOCKS blocks, all loads in flight, combined in block order.
+template <typename F>
+__device__ __forceinline__ float fold_blocks(const float* ws, int T, int c, F f) {
+  float v[FOLD_BLOCKS], acc = 0.f;
+#pragma unroll
+  for (int i = 0; i < FOLD_BLOCKS; ++i) v[i] = ws[(size_t)min(i, T - 1) * D + c];
+#pragma unroll
+  for (int i = 0; i < FOLD_BLOCKS; ++i) acc = i < T ? f(acc, v[i]) : acc;
+  return acc;
+}
+
 template <bool NT, typename V>
 __device__ __forceinline__ void store_codes(void* p, V v) {
   if constexpr (NT)
@@ -649,8 +669,9 @@ __device__ __forceinline__ void store_codes(void* p, V v) {
 // rint(x * (127/amax))), per-block symmetric E4M3 (VC_QK_FP8: scale = amax/448, code = the
 // nearest-even E4M3 of x * (448/amax), +0 for codes of zero magnitude) or MXFP4 by 32-channel
 // blocks (VC_QK_MXFP4: E8M0 scale byte floor(log2(amax)) - 2 + 127 per block).
-template <bool IS_K, bool ROPE, bool HAD, int QF, bool NT>
-__device__ __forceinline__ void quant_qk(const PrepArgs& a, float* red, uint8_t* stage) {
+template <bool IS_K, bool ROPE, bool HAD, int QF, QuantMode MODE>
+__device__ __forceinline__ void quant_qk(const PrepArgs& a, float* red, uint8_t* stage, float* fin) {
+  constexpr bool NT = MODE == STREAM;
   const int j = blockIdx.x, bh = blockIdx.y;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, k4 = lane & 3;
   const int r0 = j * BLK;
@@ -658,6 +679,17 @@ __device__ __forceinline__ void quant_qk(const PrepArgs& a, float* red, uint8_t*
   const uint16_t* X = IS_K ? a.K : a.Q;
   const int32_t* gather = IS_K ? (a.perm ? a.perm + head : nullptr) : (a.q_perm ? a.q_perm + head : nullptr);
 
+  if constexpr (IS_K && MODE == FOLD) {   // the key mean
+    if (threadIdx.x < D) {
+      const int c = threadIdx.x;
+      float m = 0.f;
+      if (a.smooth_k)
+        m = fold_blocks(a.ws_ksum + (size_t)bh * a.T * D, a.T, c, [](float s, float v) { return s + v; }) / (float)a.N;
+      fin[c] = m;
+      if (j == 0) a.k_mean[(size_t)bh * D + c] = m;
+    }
+    __syncthreads();
+  }
   float x[2][4][8];
   bool valid[2];
 #pragma unroll
@@ -671,7 +703,7 @@ __device__ __forceinline__ void quant_qk(const PrepArgs& a, float* red, uint8_t*
     if (ROPE) rope_row32(x[it], n, k4, a);
     if (IS_K) {
       // the key mean (zeros without centering: x - 0 = x)
-      const float* km = a.k_mean + (size_t)bh * D + 8 * k4;
+      const float* km = (MODE == FOLD ? fin : a.k_mean + (size_t)bh * D) + 8 * k4;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const float4 m0 = *reinterpret_cast<const float4*>(km + 32 * i);
@@ -786,15 +818,25 @@ __device__ __forceinline__ void quant_qk(const PrepArgs& a, float* red, uint8_t*
 
 // V' rows of block j: gather, subtract the block mean (bf16; zeros without demeaning), scale per
 // channel, E4M3 RNE, transposed through LDS into the tile order of the attention kernel.
-template <bool NT>
-__device__ __forceinline__ void quant_v(const PrepArgs& a, uint8_t (*vt)[D + 8]) {
+template <QuantMode MODE>
+__device__ __forceinline__ void quant_v(const PrepArgs& a, uint8_t (*vt)[D + 8], float* fin) {
+  constexpr bool NT = MODE == STREAM;
   const int j = blockIdx.x, bh = blockIdx.y;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, k4 = lane & 3;
   const int r0 = j * BLK;
   const size_t head = (size_t)bh * a.N;
   const int32_t* gather = a.perm ? a.perm + head : nullptr;
   const uint16_t* mu = a.v_mean + ((size_t)bh * a.T + j) * D + 8 * k4;
-  const float* vinv = a.ws_vinv + (size_t)bh * D + 8 * k4;
+  if constexpr (MODE == FOLD) {   // the inverse value scales
+    if (threadIdx.x < D) {
+      const int c = threadIdx.x;
+      const float amax = fold_blocks(a.ws_vamax + (size_t)bh * a.T * D, a.T, c, [](float s, float v) { return fmaxf(s, v); });
+      fin[c] = amax > 0.f ? 448.f / amax : 0.f;
+      if (j == 0) a.v_scale[(size_t)bh * D + c] = amax > 0.f ? amax / 448.f : 1.f;
+    }
+    __syncthreads();
+  }
+  const float* vinv = (MODE == FOLD ? fin : a.ws_vinv + (size_t)bh * D) + 8 * k4;
 #pragma unroll
   for (int it = 0; it < 2; ++it) {
     const int rl = wave * 32 + it * 16 + (lane >> 2);
@@ -843,18 +885,19 @@ __device__ __forceinline__ void quant_v(const PrepArgs& a, uint8_t (*vt)[D + 8])
 }
 
 // grid (T, B*H, 3): z = 0 K' rows, z = 1 V' rows, z = 2 Q rows of block blockIdx.x.
-template <bool ROPE, bool HAD, int QF, bool NT>
+template <bool ROPE, bool HAD, int QF, QuantMode MODE>
 __global__ __launch_bounds__(256) void prep_quant(PrepArgs a) {
+  __shared__ __attribute__((aligned(16))) float fin[MODE == FOLD ? D : 4];   // the head's key mean or inverse value scales
   __shared__ float red[4];
   // V codes of the block, row-major (8-byte rows), for the transpose; MX scale bytes of a Q/K block
   __shared__ uint8_t vt[BLK][D + 8];
   // K' and V' first: their rows were just read by the statistics pass and may still be cached
   if (blockIdx.z == 0)
-    quant_qk<true, ROPE, HAD, QF, NT>(a, red, &vt[0][0]);
+    quant_qk<true, ROPE, HAD, QF, MODE>(a, red, &vt[0][0], fin);
   else if (blockIdx.z == 1)
-    quant_v<NT>(a, vt);
+    quant_v<MODE>(a, vt, fin);
   else
-    quant_qk<false, ROPE, HAD, QF, NT>(a, red, &vt[0][0]);
+    quant_qk<false, ROPE, HAD, QF, MODE>(a, red, &vt[0][0], fin);
 }
 
 hipError_t launch_prep(const PrepArgs& a, int BH, hipStream_t s) {
@@ -868,35 +911,38 @@ hipError_t launch_prep(const PrepArgs& a, int BH, hipStream_t s) {
     prep_stats_walk<true><<<sgrid, 64, 0, s>>>(a);
   else
     prep_stats_walk<false><<<sgrid, 64, 0, s>>>(a);
-  prep_finalize<<<dim3(BH, 16), 256, 0, s>>>(a);
+  const QuantMode mode = (long long)a.T * BH > STREAM_BLOCKS ? STREAM : a.T <= FOLD_BLOCKS ? FOLD : KEEP;
+  if (mode != FOLD) prep_finalize<<<dim3(BH, 16), 256, 0, s>>>(a);
   const dim3 grid(a.T, BH, 3);
-  auto quant = [&](auto QFC, auto NTC) {
+  auto quant = [&](auto QFC, auto MC) {
     constexpr int qf = decltype(QFC)::value;
-    constexpr bool nt = decltype(NTC)::value;
+    constexpr QuantMode md = decltype(MC)::value;
     if (a.rope) {
       if (a.hadamard)
-        prep_quant<true, true, qf, nt><<<grid, 256, 0, s>>>(a);
+        prep_quant<true, true, qf, md><<<grid, 256, 0, s>>>(a);
       else
-        prep_quant<true, false, qf, nt><<<grid, 256, 0, s>>>(a);
+        prep_quant<true, false, qf, md><<<grid, 256, 0, s>>>(a);
     } else {
       if (a.hadamard)
-        prep_quant<false, true, qf, nt><<<grid, 256, 0, s>>>(a);
+        prep_quant<false, true, qf, md><<<grid, 256, 0, s>>>(a);
       else
-        prep_quant<false, false, qf, nt><<<grid, 256, 0, s>>>(a);
+        prep_quant<false, false, qf, md><<<grid, 256, 0, s>>>(a);
     }
   };
-  auto format = [&](auto NTC) {
+  auto format = [&](auto MC) {
     if (a.qk_fmt == VC_QK_MXFP4)
-      quant(std::integral_constant<int, VC_QK_MXFP4>{}, NTC);
+      quant(std::integral_constant<int, VC_QK_MXFP4>{}, MC);
     else if (a.qk_fmt == VC_QK_FP8)
-      quant(std::integral_constant<int, VC_QK_FP8>{}, NTC);
+      quant(std::integral_constant<int, VC_QK_FP8>{}, MC);
     else
-      quant(std::integral_constant<int, VC_QK_INT8>{}, NTC);
+      quant(std::integral_constant<int, VC_QK_INT8>{}, MC);
   };
-  if ((long long)a.T * BH > STREAM_BLOCKS)
-    format(std::integral_constant<bool, true>{});
+  if (mode == STREAM)
+    format(std::integral_constant<QuantMode, STREAM>{});
+  else if (mode == FOLD)
+    format(std::integral_constant<QuantMode, FOLD>{});
   else
-    format(std::integral_constant<bool, false>{});
+    format(std::integral_constant<QuantMode, KEEP>{});
   return hipGetLastError();
 }
 

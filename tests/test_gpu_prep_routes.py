@@ -84,3 +84,20 @@ def test_infinity_in_the_last_row_of_a_ragged_block(H):
     o = oracle.prep(Q[:, :1], K[:, :1], V[:, :1], grid)["v_mean"]
     assert o[0, 0, 1, 3] == 0x7f80
     assert all(np.array_equal(m[0, h], o[0, 0]) for h in range(H))
+
+
+@pytest.mark.parametrize("N,opt", [(2048, {}), (2049, {}), (1921, dict(smooth_k=False)), (2177, dict(smooth_v=False)), (127, {})])
+def test_head_statistics_folded_and_not(N, opt):
+    """16 and 17 blocks per head: the quantization forms the key mean and value scales itself, or reads them."""
+    Q, K, V = rand_qkv(1, 2, N, 3 * N)
+    V[0, 1, :, 5] = V[0, 1, 0, 5]   # a constant channel: zero residual, scale 1
+    perm = S.random_perm(N, N, 1, 2)
+    A = vc.Attention(1, 2, (1, 1, N), vc.make_opts(**opt), vc.make_group_opts(mode=vc.GROUP_IDENTITY))
+    A.ws.fill_(0x5a)
+    A.prep(dev16(Q), dev16(K), dev16(V), perm=dev32(perm))
+    torch.cuda.synchronize()
+    P = A.prepped
+    got = dict(q=untile_qk(P.q.cpu().numpy()), q_scale=P.q_scale.cpu().numpy(), k=untile_qk(P.k.cpu().numpy()),
+               k_scale=P.k_scale.cpu().numpy(), k_mean=P.k_mean.cpu().numpy(), v=untile_v(P.v.cpu().numpy()),
+               v_scale=P.v_scale.cpu().numpy(), v_mean=P.v_mean.cpu().numpy().view(np.uint16))
+    assert_prep_equal(got, oracle.prep(Q, K, V, (1, 1, N), perm=perm, **opt), f"N={N}")
