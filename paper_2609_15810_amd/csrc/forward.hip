@@ -973,8 +973,9 @@ __global__ __launch_bounds__(64 * SPLIT) __attribute__((amdgpu_waves_per_eu(2, 2
     }
     if (t == T - 1) mask_tile(s, kh, a.N - t * BLK);
   };
-  // the running maximum m after the tile in s, and the tile's score scale
-  auto tile_max = [&](float m, float& a_s) __attribute__((always_inline)) -> float {
+  // the maximum of the tile in s, and its score scale. The halves of the wave exchange their keys'
+  // maxima, so every lane has to be active
+  auto tile_max = [&](float& a_s) __attribute__((always_inline)) -> float {
     a_s = MX ? a.kappa : (sq * ksc) * a.kappa;
     E mk[4];
 #pragma unroll
@@ -984,14 +985,15 @@ __global__ __launch_bounds__(64 * SPLIT) __attribute__((amdgpu_waves_per_eu(2, 2
       for (int r = 2; r < 16; r += 2) v = smax3(v, s[kb][r], s[kb][r + 1]);
       mk[kb] = v;
     }
-    return fmaxf(m, (float)half_max(smax(smax(mk[0], mk[1]), smax(mk[2], mk[3]))) * a_s);
+    return (float)half_max(smax(smax(mk[0], mk[1]), smax(mk[2], mk[3]))) * a_s;
   };
 
   float m_run = -INFINITY, l_run = 0.f, a_s = 0.f;
   for (int t = t1 - 1; t >= t0; --t) {
     scores(t);
-    if (t == 0 && kh == 0) m_first[col] = tile_max(-INFINITY, a_s);   // see the epilogue
-    m_run = tile_max(m_run, a_s);
+    const float m = tile_max(a_s);
+    if (t == 0 && kh == 0) m_first[col] = fmaxf(-INFINITY, m);   // see the epilogue
+    m_run = fmaxf(m_run, m);
   }
   if (kh == 0) mch[wave][col] = m_run;
   __syncthreads();
@@ -1021,7 +1023,7 @@ __global__ __launch_bounds__(64 * SPLIT) __attribute__((amdgpu_waves_per_eu(2, 2
     if (t > t0) scores(t);
     const uint8_t* vt = vbase + (size_t)t * TILE_BYTES;
     const int slot = (t - t0) & 7;
-    const float m_new = tile_max(m_run, a_s);
+    const float m_new = fmaxf(m_run, tile_max(a_s));
     const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
     const float mul = PMODE == 0 ? a_s * 0x1p-21f : a_s;
     const float add = PMODE == 0 ? __builtin_fmaf(m_new, -0x1p-21f, a.cbias * 0x1p-24f) : -m_new;

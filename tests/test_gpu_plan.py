@@ -55,3 +55,27 @@ def test_split_key_codes(N):
     pp = oracle.prep(Q, K, V, (1, 1, N))
     assert_codes_equal(g, oracle.attention_codes(pp, rows), rows, f"N={N}")
     assert np.array_equal(O1, O2)
+
+
+@pytest.mark.parametrize("low", [0, 1])
+def test_split_key_domain_needs_all_keys_of_the_first_tile(low):
+    """Rows whose first key tile has all scores of one lane half's keys below -2^27 (log2 units) and those of
+    the other half at 0: their maximum is in the domain, so they are the method's result and not NaN."""
+    N, H = 300, 2
+    rng = np.random.default_rng(21 + low)
+    half = (np.arange(N) >> 2) & 1                       # the lane half that holds a key's score
+    k = np.where((half == low) & (np.arange(N) < 128), -1000.0, 0.0)
+    Q = S.bf16_bits(np.full((1, H, N, 128), 1000.0, np.float32))
+    K = S.bf16_bits(np.broadcast_to(k[None, None, :, None], (1, H, N, 128)).astype(np.float32))
+    V = S.bf16_bits(rng.standard_normal((1, H, N, 128)).astype(np.float32))
+    opt = dict(rope=False, hadamard=False, smooth_k=False)
+    g, O1, O2 = gpu_codes(Q, K, V, (1, 1, N), sm_scale=1.0, **opt)
+    pp = oracle.prep(Q, K, V, (1, 1, N), **opt)
+    rows = np.arange(N)
+    score = float(pp["q_scale"].flat[0] * pp["k_scale"].flat[0]) * -(127.0 ** 2) * 128 * np.log2(np.e)
+    assert score < -(2.0 ** 27)                          # the premise: that half is beyond the domain's limit
+    assert_codes_equal(g, oracle.attention_codes(pp, rows, sm_scale=1.0), rows, f"half {low}")
+    o = S.bits_to_f32(O2.view(np.uint16)).reshape(H, N, 128).astype(np.float64)
+    assert np.isfinite(o).all()
+    check_output(o, oracle.attention(pp, rows, sm_scale=1.0), f"half {low}")
+    assert np.array_equal(O1, O2)
