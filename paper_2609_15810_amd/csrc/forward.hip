@@ -1135,44 +1135,49 @@ hipError_t launch_fp8_score_product(const uint8_t* a, const uint8_t* b, const fl
 }
 
 // How the rows are dealt out: in order of head and query, n8 workgroups of 256 queries, then n4 of
-// 128, then attn_split on groups of 32. A CU holds one workgroup of any kind, so what counts is
-// rounds of 256 workgroups times the length of a round. Measured per key tile (INT8): 256 queries
+// 128, then n1 of attn_split on groups of 32. A CU holds one workgroup of any kind, so what counts is
+// rounds of 256 workgroups times the length of a round. Measured per key tile (INT8, ExpCast): 256 queries
 // 1.8 us (8 waves, two per SIMD), 128 queries 1.31 us (a lone wave per SIMD waits for its own latencies),
-// attn_split 0.65 us while a head's K and V fit an XCD's L2 and 1.1 us beyond; a second launch costs
+// attn_split 0.65..0.8 us while a head's K and V fit an XCD's L2 and 0.9..1.1 us beyond; a second launch costs
 // about 5 us. Full rounds go to the 256-query kernel; the rest, which would be a round of its own,
 // to whichever ends first. Two heads of 1024 tokens (8 workgroups before): 22.1 -> 11.5 us; one head of
 // 5850 (23): 79 -> 38; two: 82 -> 61; one of 32760 (128): 399 -> 304; 24 of 5850 (552, 2.2 rounds):
-// 276 -> 259; 7 of 13833 (385): 388 -> 350, with the exponential path 490 -> 404. The choice depends on the shape alone, so the code-dumping variant makes the same one.
-struct Plan {
-  int n8, n4;
-};
-static Plan plan(int N, int BH) {
+// 276 -> 259; 7 of 13833 (385): 388 -> 350, with the exponential path 490 -> 404.
+// Up to two key tiles attn_split has nothing to split (six waves without a tile, all exchanges and
+// both passes): one head of 129..256 tokens takes it 10.3..12.2 us over formats and paths, the 128-query
+// kernel 9.2..9.9, the 256-query one 10.1..13.9; from three tiles on it is the faster one (9.8..10.9
+// against 9.9..11.5).
+// The choice depends on the shape alone, so the code-dumping variant makes the same one.
+ForwardPlan forward_plan(int N, int BH) {
   constexpr int CUS = 256;
   const int per8 = (N + 255) / 256, per4 = (N + 127) / 128, per1 = (N + 31) / 32;
   const int T = per4, w8 = per8 * BH, full = w8 / CUS * CUS;
   auto rounds = [](int wgs) { return (float)((wgs + CUS - 1) / CUS); };
-  if (full == w8) return {w8, 0};
-  const int u4 = BH * per4 - (full / per8 * per4 + min(full % per8 * 2, per4));   // left for the other kernels
-  const int u1 = BH * per1 - (full / per8 * per1 + min(full % per8 * 8, per1));
-  const float extra = full > 0 ? 5.f : 0.f;
-  const float t8 = 1.8f * T, t4 = rounds(u4) * 1.31f * T + extra, t1 = rounds(u1) * (N <= 16384 ? 0.7f : 1.1f) * T + extra + 1.f;
-  if (t1 < t8 && t1 < t4) return {full, 0};
-  return t4 < t8 ? Plan{full, u4} : Plan{w8, 0};
+  // the first workgroup of 128 and of 32 queries behind n8 workgroups of 256
+  auto after8 = [&](int n8, int per, int parts) { return n8 / per8 * per + min(n8 % per8 * parts, per); };
+  const int all4 = BH * per4, all1 = BH * per1;
+  const ForwardPlan only8{w8, all4, 0, all1, 0};
+  if (full == w8) return only8;
+  const int f4 = after8(full, per4, 2), f1 = after8(full, per1, 8);
+  const float r4 = rounds(all4 - f4), r1 = rounds(all1 - f1), extra = full > 0 ? 5.f : 0.f;
+  const float t8 = 1.8f * T, t4 = r4 * 1.31f * T + extra, t1 = r1 * (N <= 16384 ? 0.7f : 1.1f) * T + extra + 1.f;
+  const bool split = T > 2 && t1 < t8 && t1 < t4;
+  if (!split && t4 >= t8) return only8;
+  if (split) return {full, f4, 0, f1, all1 - f1};
+  return {full, f4, all4 - f4, all1, 0};
 }
 
 hipError_t launch_forward(FwdArgs a, int BH, hipStream_t s) {
-  const int per8 = (a.N + 255) / 256, per4 = (a.N + 127) / 128, per1 = (a.N + 31) / 32;
-  const auto [n8, n4] = plan(a.N, BH);
+  const ForwardPlan p = forward_plan(a.N, BH);
   auto go = [&](auto PC, auto QC, auto DC) {
     constexpr int pm = decltype(PC)::value, qf = decltype(QC)::value;
     constexpr bool dump = decltype(DC)::value;
     a.first = 0;
-    if (n8 > 0) attn_fwd<pm, qf, 8, dump><<<n8, 512, 0, s>>>(a);
-    a.first = n8 / per8 * per4 + min(n8 % per8 * 2, per4);
-    const int end4 = a.first + n4;
-    if (n4 > 0) attn_fwd<pm, qf, 4, dump><<<n4, 256, 0, s>>>(a);
-    a.first = end4 / per4 * per1 + min(end4 % per4 * 4, per1);
-    if (a.first < BH * per1) attn_split<pm, qf, dump><<<BH * per1 - a.first, 64 * SPLIT, 0, s>>>(a);
+    if (p.n8 > 0) attn_fwd<pm, qf, 8, dump><<<p.n8, 512, 0, s>>>(a);
+    a.first = p.first4;
+    if (p.n4 > 0) attn_fwd<pm, qf, 4, dump><<<p.n4, 256, 0, s>>>(a);
+    a.first = p.first1;
+    if (p.n1 > 0) attn_split<pm, qf, dump><<<p.n1, 64 * SPLIT, 0, s>>>(a);
   };
   auto fmt = [&](auto PC, auto DC) {
     if (a.qk_fmt == VC_QK_MXFP4) go(PC, std::integral_constant<int, VC_QK_MXFP4>{}, DC);

@@ -49,6 +49,13 @@ struct FwdArgs {
   int first;        // a launch's first workgroup (in order of head and query)
 };
 
+// How a call's rows are dealt to the attention kernels: n8 workgroups of 256 queries, n4 of 128 and n1 of
+// 32, each counted in order of head and query (a head's last workgroup may be ragged); first4 and first1 are
+// the positions of the first ones behind those before them.
+struct ForwardPlan {
+  int n8, first4, n4, first1, n1;
+};
+
 struct GroupArgs {
   const uint16_t* V;
   float* centroids;
@@ -68,9 +75,13 @@ struct GroupArgs {
 };
 
 hipError_t launch_prep(const PrepArgs& a, int BH, hipStream_t s);
+ForwardPlan forward_plan(int N, int BH);
 hipError_t launch_forward(FwdArgs a, int BH, hipStream_t s);
 hipError_t launch_group(const GroupArgs& a, int BH, hipStream_t s);
 hipError_t launch_fp8_score_product(const uint8_t* a, const uint8_t* b, const float* c_in, float* out, int n,
                                     hipStream_t s);
 
 }  // namespace vc
+
+// The plan of a shape, for tests on the host (not part of the public ABI): n8, first4, n4, first1, n1.
+extern "C" void vc_internal_forward_plan(int32_t N, int32_t BH, int32_t plan[5]);
