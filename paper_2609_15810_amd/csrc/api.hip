@@ -394,8 +394,8 @@ vc_status vc_fp8_score_product(const uint8_t* a, const uint8_t* b, const float* 
   return hip_status(vc::launch_fp8_score_product(a, b, c_in, out, n, static_cast<hipStream_t>(stream)));
 }
 
-void vc_internal_forward_plan(int32_t N, int32_t BH, int32_t plan[5]) {
-  const vc::ForwardPlan p = vc::forward_plan(N, BH);
+void vc_internal_forward_plan(int32_t N, int32_t BH, int32_t qk_fmt, int32_t p_mode, int32_t plan[5]) {
+  const vc::ForwardPlan p = vc::forward_plan(N, BH, qk_fmt, p_mode);
   plan[0] = p.n8, plan[1] = p.first4, plan[2] = p.n4, plan[3] = p.first1, plan[4] = p.n1;
 }
 

@@ -1147,8 +1147,29 @@ hipError_t launch_fp8_score_product(const uint8_t* a, const uint8_t* b, const fl
 // both passes): one head of 129..256 tokens takes it 10.3..12.2 us over formats and paths, the 128-query
 // kernel 9.2..9.9, the 256-query one 10.1..13.9; from three tiles on it is the faster one (9.8..10.9
 // against 9.9..11.5).
-// The choice depends on the shape alone, so the code-dumping variant makes the same one.
-ForwardPlan forward_plan(int N, int BH) {
+// The estimates up to here are those of INT8 with ExpCast. For a call without a full round the order is the
+// same for all formats and paths: heads of 8192 tokens, 256 queries / 128 / attn_split in us, one head
+// (one round of each) and two (two rounds of attn_split):
+//   INT8   108 / 81 / 51, 114 / 85 / 98     exponential   151 / 106 / 57, 154 / 109 / 110
+//   FP8     96 / 74 / 43, 103 / 78 / 85     exponential   138 / 97 / 48, 142 / 100 / 91
+//   MXFP4   91 / 75 / 38, 96 / 78 / 72      exponential   135 / 101 / 42, 138 / 101 / 78
+// (two rounds go to the 128-query kernel, which MXFP4 and the exponential path with FP8 would end sooner with
+// attn_split; none is slower than the 256-query kernel alone).
+// Behind full rounds a second launch waits for the last workgroup of the first, whereas further
+// workgroups of the same launch start as CUs fall free. A head's last workgroup ends early by the rows past the
+// head's end (zero scores, nothing to rescale), so R full rounds free 0.37 R / workgroups per head of a round
+// for each such workgroup, times the share of its rows that are past the end, and a rest within that costs the 256-query kernel
+// little: 103 heads of 1051 tokens (515 workgroups) take 74 us without a second launch and 78 with, 205
+// heads 114 and 126, 57 heads of 2060 110 and 113. So there the 256-query kernel keeps the rest unless the format's own
+// times per key tile (per 8 key tiles for attn_split, whose longest wave walks that many; each behind full rounds,
+// launch included) are below what it still costs. Of 798 calls measured over 1 to 8 full rounds 42 were more than 1% slower
+// than the 256-query kernel alone (up to 11%), now 10 (up to 1.7%); 4 others lose by the rule (up to 2.4%).
+struct RestTimes {
+  float t8, t4, t1;
+};
+constexpr RestTimes REST_TIMES[2][3] = {{{1.51f, 1.13f, 8.0f}, {1.32f, 1.03f, 5.7f}, {1.26f, 1.06f, 5.3f}},    // ExpCast: INT8, FP8, MXFP4
+                                        {{2.18f, 1.53f, 8.5f}, {1.98f, 1.39f, 6.4f}, {1.96f, 1.43f, 6.2f}}};   // exponential
+ForwardPlan forward_plan(int N, int BH, int qk_fmt, int p_mode) {
   constexpr int CUS = 256;
   const int per8 = (N + 255) / 256, per4 = (N + 127) / 128, per1 = (N + 31) / 32;
   const int T = per4, w8 = per8 * BH, full = w8 / CUS * CUS;
@@ -1163,12 +1184,19 @@ ForwardPlan forward_plan(int N, int BH) {
   const float t8 = 1.8f * T, t4 = r4 * 1.31f * T + extra, t1 = r1 * (N <= 16384 ? 0.7f : 1.1f) * T + extra + 1.f;
   const bool split = T > 2 && t1 < t8 && t1 < t4;
   if (!split && t4 >= t8) return only8;
+  if (full > 0) {
+    const RestTimes& t = REST_TIMES[p_mode][qk_fmt];
+    const float past = (float)(per8 * 256 - N) / 256.f;
+    const float freed = 0.37f * (full / CUS) * past / per8 - 0.0029f * (w8 - full);
+    const float own = split ? r1 * t.t1 * ((T + 7) / 8) * (N <= 16384 ? 1.f : 1.35f) : r4 * t.t4 * T;
+    if (own + 0.4f >= t.t8 * T * fminf(1.f, 1.f - freed)) return only8;
+  }
   if (split) return {full, f4, 0, f1, all1 - f1};
   return {full, f4, all4 - f4, all1, 0};
 }
 
 hipError_t launch_forward(FwdArgs a, int BH, hipStream_t s) {
-  const ForwardPlan p = forward_plan(a.N, BH);
+  const ForwardPlan p = forward_plan(a.N, BH, a.qk_fmt, a.p_mode);
   auto go = [&](auto PC, auto QC, auto DC) {
     constexpr int pm = decltype(PC)::value, qf = decltype(QC)::value;
     constexpr bool dump = decltype(DC)::value;

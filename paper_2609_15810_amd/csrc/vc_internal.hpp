@@ -75,7 +75,7 @@ struct GroupArgs {
 };
 
 hipError_t launch_prep(const PrepArgs& a, int BH, hipStream_t s);
-ForwardPlan forward_plan(int N, int BH);
+ForwardPlan forward_plan(int N, int BH, int qk_fmt, int p_mode);
 hipError_t launch_forward(FwdArgs a, int BH, hipStream_t s);
 hipError_t launch_group(const GroupArgs& a, int BH, hipStream_t s);
 hipError_t launch_fp8_score_product(const uint8_t* a, const uint8_t* b, const float* c_in, float* out, int n,
@@ -83,5 +83,5 @@ hipError_t launch_fp8_score_product(const uint8_t* a, const uint8_t* b, const fl
 
 }  // namespace vc
 
-// The plan of a shape, for tests on the host (not part of the public ABI): n8, first4, n4, first1, n1.
-extern "C" void vc_internal_forward_plan(int32_t N, int32_t BH, int32_t plan[5]);
+// The plan of a call, for tests on the host (not part of the public ABI): n8, first4, n4, first1, n1.
+extern "C" void vc_internal_forward_plan(int32_t N, int32_t BH, int32_t qk_fmt, int32_t p_mode, int32_t plan[5]);
