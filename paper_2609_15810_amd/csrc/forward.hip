@@ -247,6 +247,18 @@ __device__ __forceinline__ int code4(const SV& s, int d4, float mul, float add) 
   }
 }
 
+// ExpCast codes of four scores by the saturating byte conversion, mul = 8a, add = fl(cbias - 8m'): the same codes
+// (above 255 it saturates, which the clip brings to 120 likewise) in a chain of four conversions. Where no
+// products stand beside them (prologue and tail iterations) they are the shorter way: 132 heads of 367 tokens
+// (three tiles, two rounds of workgroups) 27.8 us against 28.2 with code4.
+template <typename SV>
+__device__ __forceinline__ int code4_bytes(const SV& s, int d4, float mul, float add) {
+  uint32_t w = 0;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) w = __builtin_amdgcn_cvt_pk_u8_f32(__builtin_fmaf((float)s[4 * d4 + q], mul, add), q, w);
+  return (int)w;
+}
+
 // Position of workgroup id in the order in which the grid is worked through: the dispatcher deals
 // workgroups to the XCDs round-robin by linear id, and this bijection gives each XCD a contiguous
 // range, so that its L2 serves one or two heads' K/V tiles instead of every head's.
@@ -377,8 +389,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   __shared__ float m_first[NW][32];  // each query's running maximum after tile 0
 
   // half the HBM fetches of the plain order; the time is unchanged, the kernel is not memory-bound
-  const int wg = a.first + xcd_order(blockIdx.x, gridDim.x);
-  const int per_head = (a.N + NQ - 1) / NQ, bh = wg / per_head, qt = wg - bh * per_head;
+  const uint32_t wg = a.first + xcd_order(blockIdx.x, gridDim.x), per_head = ((uint32_t)a.N + NQ - 1) / NQ;
+  const int bh = wg / per_head, qt = wg - bh * per_head;   // unsigned: the shorter division
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int kh = lane >> 5, col = lane & 31;
@@ -550,12 +562,13 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     mx = half_max(mx);
     m_new = fmaxf(m_run, (float)mx * a_s);
     alpha = __builtin_amdgcn_exp2f(m_run - m_new);
-    const float mul = PMODE == 0 ? a_s * 0x1p-21f : a_s;
-    const float add = PMODE == 0 ? __builtin_fmaf(m_new, -0x1p-21f, a.cbias * 0x1p-24f) : -m_new;
+    const float mul = PMODE == 0 ? 8.f * a_s : a_s;
+    const float add = PMODE == 0 ? a.cbias - 8.f * m_new : -m_new;
 #pragma unroll
     for (int kb = 0; kb < 4; ++kb)
 #pragma unroll
-      for (int d4 = 0; d4 < 4; ++d4) pn[kb >> 1][4 * (kb & 1) + d4] = code4<PMODE>(s[kb], d4, mul, add);
+      for (int d4 = 0; d4 < 4; ++d4)
+        pn[kb >> 1][4 * (kb & 1) + d4] = PMODE == 0 ? code4_bytes(s[kb], d4, mul, add) : code4<1>(s[kb], d4, mul, add);
     if (PMODE == 0 && __builtin_amdgcn_ballot_w64(fabsf(m_new) >= WIDE_MAX)) clip_codes(pn);
     if (decltype(LASTC)::value) clear_padded(pn, kh, a.N - t * BLK);
   };
