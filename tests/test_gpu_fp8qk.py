@@ -227,7 +227,8 @@ def test_forward_f8_ragged_perm(flags):
 
 @pytest.mark.parametrize("N", [1, 100, 129, 300, 500, 513, 700, 833, 1100, 1400, 1900, 2500])
 def test_forward_f8_tile_counts(N):
-    """Tile counts 1..11 and 20 with ragged last tiles: every remainder of the unrolled tile loop."""
+    """Tile counts 1..11 and 20 with ragged last tiles, by the kernels that a call of few heads takes (every
+    kernel at its loop's remainders: test_gpu_attn_kernels.py)."""
     Q, K, V = rand_qkv(1, 2, N, 400 + N)
     A, _ = gpu_prep_f8(Q, K, V, (1, 1, N))
     o = gpu_forward(A).reshape(2, N, 128)

@@ -175,8 +175,10 @@ def test_forward_ragged_perm(flags):
 
 @pytest.mark.parametrize("N", [1, 100, 129, 200, 257, 300, 500, 513, 600, 700, 833, 1100, 1280, 1400, 1900, 2100, 2500])
 def test_forward_tile_counts(N):
-    """Every key-tile count from 1 to 11 and 17 (so every remainder of the tile loop, mean batches
-    of 8 that end full or partial) with a ragged last tile where N is not a multiple of 128."""
+    """Every key-tile count from 1 to 11 and 17 (mean batches of 8 that end full or partial) with a
+    ragged last tile where N is not a multiple of 128, by the kernels that a call of two heads takes
+    (the 128-query one up to two tiles, then the key split; every kernel at its loop's remainders:
+    test_gpu_attn_kernels.py)."""
     grid = (1, 1, N)
     rng = np.random.default_rng(100 + N)
     Q = S.bf16_bits((rng.standard_normal((1, 2, N, 128)) * 2).astype(np.float32))

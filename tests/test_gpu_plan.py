@@ -47,7 +47,7 @@ def test_rows_dealt_to_each_kernel(H, N, fmt, p_mode, heads):
     check_output(o[sel][:, rows], oracle.attention(pp, rows, p_mode=p_mode), f"{H}x{N} {fmt}")
 
 
-@pytest.mark.parametrize("N", [64, 257, 1025, 2000])   # one to two tiles per wave, waves without a tile
+@pytest.mark.parametrize("N", [64, 257, 1025, 2000])   # 64: not split; else one to two tiles per wave, waves without a tile
 def test_split_key_codes(N):
     Q, K, V = rand_qkv(1, 2, N, 5 * N)
     g, O1, O2 = gpu_codes(Q, K, V, (1, 1, N))
