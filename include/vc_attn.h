@@ -238,7 +238,12 @@ vc_status vc_attn_prep_noalloc(const vc_shape *shape, const vc_opts *opts, const
  * Domain: with p_mode = VC_P_EXPCAST, a query row whose running maximum score in log2 units
  * (sm_scale * log2(e) * q.k of the quantized operands) reaches 2^27 in magnitude, i.e. softmax
  * logits beyond about 9.3e7, is outside the supported domain: its output row is written as NaN.
- * Every other row is the method's result (codes exactly those of eq. direct-fp8). */
+ * Every other row is the method's result (codes exactly those of eq. direct-fp8).
+ * Reproducibility: the same operands, shape and options give the same bits in every call. The rows
+ * are dealt to kernels by B*H and N together, so the same head in calls of different B*H (alone, or
+ * as part of a shard) has the same probability codes, but its O can differ by the order of the fp32
+ * sums and of the block means' batches: at most 2^-15 of the largest value magnitude before the
+ * rounding to bf16, so that and one bf16 step after it. */
 vc_status vc_attn_forward(const vc_shape *shape, const vc_opts *opts, const vc_prepped *in,
                           const int32_t *q_perm, uint16_t *O, void *stream);
 
