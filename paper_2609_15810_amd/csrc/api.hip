@@ -62,13 +62,35 @@ size_t prep_ws(const vc_shape* s) {
   return 2 * align256(BH * T * kD * 4) + align256(BH * kD * 4);
 }
 
-// At least what vc_attn_group carves up below (callers hold buffers of this size).
+// The k-means workspace: byte offsets of its parts (each 256-byte aligned) and its size.
+struct GroupLayout {
+  size_t codes, scale, cent8, sums, amax_part, hist, bytes;
+  int nblk, sums_head, nsort;   // see vc::GroupArgs
+};
+GroupLayout group_layout(const vc_shape* s, int k) {
+  GroupLayout l;
+  const size_t BH = (size_t)s->B * s->H;
+  l.nblk = blocks_of(s->N, 256);
+  l.sums_head = (k * (kD + 1) + 3) & ~3;
+  l.nsort = blocks_of(s->N, 1024);
+  size_t end = 0;
+  auto part = [&](size_t bytes) {
+    const size_t at = end;
+    end += align256(bytes);
+    return at;
+  };
+  l.codes = part(BH * s->N * kD);
+  l.scale = part(BH * 4);
+  l.cent8 = part(2 * BH * k * kD);
+  l.sums = part(3 * BH * l.sums_head * 4);
+  l.amax_part = part(BH * l.nblk * 4);
+  l.hist = part(BH * l.nsort * k * 4);
+  l.bytes = end;
+  return l;
+}
+
 size_t group_ws(const vc_shape* s, const vc_group_opts* g) {
-  if (g->mode != VC_GROUP_KMEANS) return 0;
-  const size_t BH = (size_t)s->B * s->H, N = s->N, K = g->k, nblk = blocks_of(s->N, 256);
-  return align256(BH * N * kD) + align256(BH * 4) + align256(BH * K * kD * 4) + align256(BH * nblk * K * kD * 4) +
-         2 * align256(BH * nblk * K * 4) + align256(BH * 64 * kD) +
-         align256(BH * 64 * 4);
+  return g->mode == VC_GROUP_KMEANS ? group_layout(s, g->k).bytes : 0;
 }
 
 // Tokens per k-means assignment workgroup (a multiple of 256, at most 65536: the member sums, times
@@ -222,24 +244,19 @@ vc_status vc_attn_group(const vc_shape* shape, const vc_group_opts* gopts, const
   a.cube_h = gopts->cube[1];
   a.cube_w = gopts->cube[2];
   a.BH = (int)BH;
-  a.nblk = blocks_of(shape->N, 256);
-  a.sums_head = (a.k * (kD + 1) + 3) & ~3;
-  a.nsort = blocks_of(shape->N, 1024);
   a.atok = assign_tokens((int)BH, shape->N);
   if (km) {
+    const GroupLayout l = group_layout(shape, a.k);
     char* p = static_cast<char*>(ws);
-    const size_t N = shape->N, K = a.k, nblk = a.nblk;
-    a.codes = reinterpret_cast<int8_t*>(p);
-    p += align256(BH * N * kD);
-    a.scale = reinterpret_cast<float*>(p);
-    p += align256(BH * 4);
-    a.cent8 = reinterpret_cast<int8_t*>(p);
-    p += align256(BH * K * kD * 4);
-    a.sums = reinterpret_cast<int32_t*>(p);
-    p += align256(BH * nblk * K * kD * 4);
-    a.amax_part = reinterpret_cast<float*>(p);
-    p += align256(BH * nblk * K * 4);
-    a.hist = reinterpret_cast<int32_t*>(p);
+    a.codes = reinterpret_cast<int8_t*>(p + l.codes);
+    a.scale = reinterpret_cast<float*>(p + l.scale);
+    a.cent8 = reinterpret_cast<int8_t*>(p + l.cent8);
+    a.sums = reinterpret_cast<int32_t*>(p + l.sums);
+    a.amax_part = reinterpret_cast<float*>(p + l.amax_part);
+    a.hist = reinterpret_cast<int32_t*>(p + l.hist);
+    a.nblk = l.nblk;
+    a.sums_head = l.sums_head;
+    a.nsort = l.nsort;
   }
   return hip_status(vc::launch_group(a, (int)BH, static_cast<hipStream_t>(stream)));
 }

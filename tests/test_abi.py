@@ -192,6 +192,18 @@ def test_fp8_score_product_validation(L):
     assert f(FAKE, FAKE + 4, FAKE, FAKE, 1, None) == 5
 
 
+def test_grouping_workspace_holds_what_is_used(L):
+    """Codes of every token and, beside them, three sums and two centroid buffers per head, a maximum per 256 and
+    label counts per 1024 tokens: 5.4 MB beyond the codes for 40 heads of 75600 tokens and 64 clusters."""
+    s = shape(H=40, N=75600, F=21, Ht=60, Wd=60)
+    up = lambda n: -(-n // 256) * 256
+    for k in (1, 7, 32, 64):
+        sums = -(-k * 129 // 4) * 4
+        want = up(40 * 75600 * 128) + up(40 * 4) + up(2 * 40 * k * 128) + up(3 * 40 * sums * 4) + \
+            up(40 * -(-75600 // 256) * 4) + up(40 * -(-75600 // 1024) * k * 4)
+        assert vc.workspace_size(s, None, vc.make_group_opts(k=k)) == want
+
+
 def test_workspace_size(L):
     s = vc.make_shape(1, 12, (21, 39, 40))
     o, g = vc.make_opts(), vc.make_group_opts()

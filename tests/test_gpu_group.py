@@ -47,3 +47,20 @@ def test_group_edges(H, N, k, iters, warm):
     for name in ("labels", "perm", "inv_perm"):
         assert np.array_equal(getattr(A, name).cpu().numpy(), g[name]), name
     assert np.array_equal(A.centroids.cpu().numpy().view(np.uint32), np.asarray(g["centroids"], np.float32).view(np.uint32))
+
+
+@pytest.mark.parametrize("H,N,k,iters", [(2, 700, 32, 3), (2, 1025, 64, 3), (1, 1026, 1, 2), (3, 2050, 33, 1), (5, 4097, 7, 4)])
+def test_workspace_of_exactly_its_size(H, N, k, iters):
+    """Nothing behind the workspace is written, and what its parts hold suffices."""
+    V = values(H, N, 3 * N + k)
+    A = vc.Attention(1, H, (1, 1, N), gopts=vc.make_group_opts(k=k, iters=iters))
+    need = vc.workspace_size(A.shape, None, A.gopts)
+    whole = torch.full((need + 65536,), 0x5a, dtype=torch.uint8, device="cuda")
+    A.ws = whole[:need]
+    A.group(torch.from_numpy(V.view(np.int16)).cuda())
+    torch.cuda.synchronize()
+    assert (whole[need:] == 0x5a).all()
+    g = oracle.group(V, (1, 1, N), k=k, iters=iters)
+    for name in ("labels", "perm", "inv_perm"):
+        assert np.array_equal(getattr(A, name).cpu().numpy(), g[name]), name
+    assert np.array_equal(A.centroids.cpu().numpy().view(np.uint32), np.asarray(g["centroids"], np.float32).view(np.uint32))
