@@ -603,12 +603,11 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     pin_state();
   };
 
-  // iteration j: value product and row sum of tile j (codes pc, V_j in vt); codes of tile j+1
-  // (SOFTC; LASTC: it is the ragged last tile); scores of tile j+2 (QKC, K_{j+2} in kt; MASKC:
-  // the last tile); pair j+3 copied into (kd, vd) (COPYC); mean j stashed; rescale to m_{j+1}
-  auto iter = [&](auto COPYC, auto SOFTC, auto QKC, auto MASKC, auto LASTC, int j, const uint8_t* vt,
-                  const uint8_t* kt, uint8_t* kd, uint8_t* vd) __attribute__((always_inline)) {
-    constexpr bool cp = decltype(COPYC)::value, soft = decltype(SOFTC)::value, doqk = decltype(QKC)::value;
+  // tail iteration j (no pair is left to copy): value product and row sum of tile j (codes pc, V_j in
+  // vt); codes of tile j+1 (SOFTC; LASTC: it is the ragged last tile); scores of tile j+2 (QKC,
+  // K_{j+2} in kt; MASKC: the last tile); mean j stashed; rescale to m_{j+1}
+  auto iter = [&](auto SOFTC, auto QKC, auto MASKC, auto LASTC, int j, const uint8_t* vt, const uint8_t* kt) __attribute__((always_inline)) {
+    constexpr bool soft = decltype(SOFTC)::value, doqk = decltype(QKC)::value;
     dump_codes(j);
     v8i vop[8];
 #pragma unroll
@@ -617,13 +616,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     rs = mfma_f8_16(ones16, pc[0], rs);
     rs = mfma_f8_16(ones16, pc[1], rs);
 #pragma unroll
-    for (int n = 0; n < 8; ++n) {
-      o[n & 3] = mfma_f8(vop[n], pc[n >> 2], o[n & 3]);
-      if (cp && n < PAIR_COPIES) load_part(n, j + 3, kd, vd);
-    }
-    if (cp)
-#pragma unroll
-      for (int k = 8; k < PAIR_COPIES; ++k) load_part(k, j + 3, kd, vd);
+    for (int n = 0; n < 8; ++n) o[n & 3] = mfma_f8(vop[n], pc[n >> 2], o[n & 3]);
     v8i pn[2];
     float alpha = 1.f, m_new = m_run;
     if (soft) softmax(LASTC, j + 1, pn, alpha, m_new);
@@ -645,7 +638,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       pc[0] = pn[0];
       pc[1] = pn[1];
     }
-    end_iter(cp ? 2 : 0);
+    end_iter(0);
   };
 
   // steady-state iteration j (codes of tile j+1 and scores of tile j+2 exist, neither is the last
@@ -657,8 +650,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   // barrier together (with equal priorities the older wave runs ahead and the other finishes the
   // iteration alone, without a partner to overlap its matrix and vector work)
   auto fence = []() __attribute__((always_inline)) { __builtin_amdgcn_sched_barrier(0); };
-  auto iter_fast = [&](auto COPYC, int j, const uint8_t* vt, const uint8_t* kt, uint8_t* kd, uint8_t* vd) __attribute__((always_inline)) {
-    constexpr bool cp = decltype(COPYC)::value;
+  auto iter_fast = [&](int j, const uint8_t* vt, const uint8_t* kt, uint8_t* kd, uint8_t* vd) __attribute__((always_inline)) {
     dump_codes(j);
     __builtin_amdgcn_s_setprio(3);
     // the pair's copies, spread over the regions
@@ -666,7 +658,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     auto hook = [&](int h) __attribute__((always_inline)) {
 #pragma unroll
       for (int k = h * PER_HOOK; k < (h + 1) * PER_HOOK; ++k)
-        if (cp && k < PAIR_COPIES) load_part(k, j + 3, kd, vd);
+        if (k < PAIR_COPIES) load_part(k, j + 3, kd, vd);
     };
     using E = std::remove_reference_t<decltype(s[0][0])>;
     auto kmax = [&](int kb) __attribute__((always_inline)) -> E {
@@ -807,7 +799,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     if (wide) clip_codes(pn);
     pc[0] = pn[0];
     pc[1] = pn[1];
-    end_iter(cp ? 2 : 0);
+    end_iter(2);
   };
 
   // prologue: K_0, K_1, pairs 0 and 1; scores of tile 0, its codes, scores of tile 1; pair 2
@@ -841,19 +833,19 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   // V_j in vb[j%4], K_{j+2} in kb[(j+2)%4], pair j+3 into (kb[(j+1)%4], vb[(j+3)%4])
   int j = 0;
   for (; j + 6 <= T - 1; j += 4) {  // the group's last iteration j + 3 still copies pair j + 6
-    iter_fast(YES, j, vb0, kb2, kb1, vb3);
-    iter_fast(YES, j + 1, vb1, kb3, kb2, vb0);
-    iter_fast(YES, j + 2, vb2, kb0, kb3, vb1);
-    iter_fast(YES, j + 3, vb3, kb1, kb0, vb2);
+    iter_fast(j, vb0, kb2, kb1, vb3);
+    iter_fast(j + 1, vb1, kb3, kb2, vb0);
+    iter_fast(j + 2, vb2, kb0, kb3, vb1);
+    iter_fast(j + 3, vb3, kb1, kb0, vb2);
   }
   if (j + 3 <= T - 1) {
-    iter_fast(YES, j, vb0, kb2, kb1, vb3);
+    iter_fast(j, vb0, kb2, kb1, vb3);
     ++j;
     if (j + 3 <= T - 1) {
-      iter_fast(YES, j, vb1, kb3, kb2, vb0);
+      iter_fast(j, vb1, kb3, kb2, vb0);
       ++j;
       if (j + 3 <= T - 1) {
-        iter_fast(YES, j, vb2, kb0, kb3, vb1);
+        iter_fast(j, vb2, kb0, kb3, vb1);
         ++j;
       }
     }
@@ -867,14 +859,14 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   };
   // tail: iterations T-3 (scores of the last tile), T-2 (codes of the last tile), T-1
   if (j == T - 3) {
-    iter(NO, YES, YES, YES, NO, j, vbuf(j & 3), kbuf((j + 2) & 3), kb0, vb0);
+    iter(YES, YES, YES, NO, j, vbuf(j & 3), kbuf((j + 2) & 3));
     ++j;
   }
   if (j == T - 2) {
-    iter(NO, YES, NO, NO, YES, j, vbuf(j & 3), kb0, kb0, vb0);
+    iter(YES, NO, NO, YES, j, vbuf(j & 3), kb0);
     ++j;
   }
-  iter(NO, NO, NO, NO, NO, T - 1, vbuf((T - 1) & 3), kb0, kb0, vb0);
+  iter(NO, NO, NO, NO, T - 1, vbuf((T - 1) & 3), kb0);
   if (a.smooth_v) flush_means(((T - 1) >> 3) & 1, (T - 1) & 7);
 
   // epilogue: O = A s_V / l, bf16, row q written to token q_perm[q] (or q)
