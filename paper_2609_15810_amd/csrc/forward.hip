@@ -1,8 +1,10 @@
 // 8-bit VC-Attention forward on gfx950 matrix cores (Sec. 3.1 eq. tiled-low-bit-attention,
 // Sec. 3.2 eq. vc-online-update, Sec. 3.3 eq. direct-fp8).
 //
-// One workgroup = 256 queries (two 128-row query blocks) of one (batch, head): eight waves of 32
-// queries, two per SIMD. Both products are computed transposed so that a lane owns one query:
+// Two kernels, three workgroup sizes (forward_plan deals the rows): attn_fwd with eight waves of 32
+// queries (256 queries, two 128-row query blocks of one (batch, head), two waves per SIMD) or with four
+// (128 queries, one wave per SIMD), described here, and attn_split, 32 queries with the keys split over
+// eight waves, described at its place. Both products are computed transposed so that a lane owns one query:
 //   S^T = K_hat Q_hat^T   INT8 MFMA 32x32x32 (A = key rows from LDS, B = the wave's queries held
 //                         in registers for the whole kernel);
 //   O^T += V_hat^T P^T    FP8 MFMA 32x32x64 (A = residual codes from LDS, B = P codes).
@@ -18,7 +20,7 @@
 // length (scheduling barriers keep the regions in order; the codes of key block kb of tile j+1
 // are formed before the scores of block kb of tile j+2 overwrite its registers). The matrix cores
 // thus run the value and score products of one wave while its vector ALU forms codes; the two
-// waves of a SIMD share both.
+// waves of a SIMD (with 256 queries) share both.
 //
 // Per score the vector ALU does one int-to-float conversion, one fp32 fma (the code is the
 // one-rounding fma(float(acc), 8a, fl(fl(120 + beta) - 8m')) of the method's fp32 formula, evaluated
@@ -905,6 +907,12 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 // first tile are there when the second begins (up to 8 tiles no score is formed twice).
 // Tiles are read from the caches straight into registers: the operands are 16-byte pieces in lane
 // order, and no other wave of the workgroup reads the same tile.
+// Bound by latency: the compiler places each operand load right before its product, so a wave waits for
+// memory 13 times in the first pass over a tile and 21 to 23 times in the second with INT8 scores (FP8 6 and 16
+// to 18, MXFP4 6 and 14 to 16), with one other wave on its SIMD to cover it. The traffic alone (K twice and V once,
+// 48 KB) would take about 0.37 us per key tile of the head at 64 bytes per cycle and CU; it takes 0.65 to 0.8
+// while a head's K and V fit an XCD's L2. The predicates of the last tile's mask, kept through the loops, spill
+// 120 to 142 scalars into vector lanes.
 // ------------------------------------------------------------------------------------------
 constexpr int SPLIT = 8;
 
@@ -1143,8 +1151,8 @@ hipError_t launch_fp8_score_product(const uint8_t* a, const uint8_t* b, const fl
 // 128, then n1 of attn_split on groups of 32. A CU holds one workgroup of any kind, so what counts is
 // rounds of 256 workgroups times the length of a round. Measured per key tile (INT8, ExpCast): 256 queries
 // 1.8 us (8 waves, two per SIMD), 128 queries 1.31 us (a lone wave per SIMD waits for its own latencies),
-// attn_split 0.65..0.8 us while a head's K and V fit an XCD's L2 and 0.9..1.1 us beyond; a second launch costs
-// about 5 us. Full rounds go to the 256-query kernel; the rest, which would be a round of its own,
+// attn_split 0.65..0.8 us while a head's K and V fit an XCD's L2 (4 MB, 16384 tokens with 8-bit K; the same line
+// serves MXFP4, whose K is half as large) and 0.9..1.1 us beyond; a second launch costs about 5 us. Full rounds go to the 256-query kernel; the rest, which would be a round of its own,
 // to whichever ends first. Two heads of 1024 tokens (8 workgroups before): 22.1 -> 11.5 us; one head of
 // 5850 (23): 79 -> 38; two: 82 -> 61; one of 32760 (128): 399 -> 304; 24 of 5850 (552, 2.2 rounds):
 // 276 -> 259; 7 of 13833 (385): 388 -> 350, with the exponential path 490 -> 404.

@@ -629,7 +629,7 @@ __device__ __forceinline__ uint32_t fp4_codes(const float (&v)[8], float mult) {
   return mag | (w & (mag + 0x77777777u) & 0x88888888u);
 }
 
-// Codes of calls with more than STREAM_BLOCKS blocks (over 60 MB) are stored past the caches (NT): kept in
+// Codes of calls with more than STREAM_BLOCKS blocks (over 60 MB; over 40 MB with MXFP4) are stored past the caches (NT): kept in
 // them they push out K and V rows that the statistics just read and that are read again here, and
 // they would be gone themselves before the attention gets to them. Smaller calls keep them for the
 // attention. Measured (us, whole preprocessing, kept / past the caches): 12 heads of 32760 tokens 131.5 /
@@ -640,8 +640,11 @@ constexpr int STREAM_BLOCKS = 1280;
 // How a call's codes and head statistics are handled: FOLD (up to FOLD_BLOCKS blocks per head, and cached
 // stores): every workgroup forms its head's key mean or value scales from the block partials itself,
 // in the order of prep_finalize, which saves that launch and its 3 us (whole preprocessing of six heads
-// of 1000 tokens 14.5 -> 12.6 us). KEEP and STREAM read them; with more blocks per head every workgroup
-// would read more partials than rows.
+// of 1000 tokens 14.5 -> 12.6 us). KEEP and STREAM read them. 16 partials are what a thread loads at once.
+// Measured with a launch of its own / folded, more than 16 in batches of 16 (us, whole preprocessing without host
+// time, 2 / 12 / 40 heads): 16 blocks per head 13.2 / 11.5, 17.7 / 14.7, 36.7 / 34.0; 24 13.8 / 12.1, 22.6 /
+// 19.8, 47.3 / 46.2; 32 13.3 / 12.3, 24.4 / 24.1, 58.5 / 57.3; 48 14.8 / 13.3, 35.1 / 32.4; 64 15.2 / 14.1, 41.6 /
+// 41.7: folding would still gain 1 to 3 us up to about 48 blocks, and its gain is gone at 64.
 enum QuantMode { FOLD, KEEP, STREAM };
 constexpr int FOLD_BLOCKS = 16;
 
